@@ -872,6 +872,8 @@ int mcmc_create(hmm_ctx *ctx, int32_t K, int32_t n_chains, int64_t T, const uint
     ok = ok && hipMemset(s->theta2, 0, sizeof(double) * CD) == hipSuccess;
     ok = ok && hipMemset(s->tw_counts, 0, sizeof(long long) * 8 * s->C) == hipSuccess;
     ok = ok && hipMemset(s->code, 0, sizeof(int32_t) * s->C) == hipSuccess;
+    // slots not reached yet are part of checkpoints: no stray memory in them
+    ok = ok && hipMemset(s->hist, 0, sizeof(float) * (size_t)s->H * CD) == hipSuccess;
     ok = ok && hipMemset(s->hist_lpost, 0, sizeof(double) * s->H * s->C) == hipSuccess;
     ok = ok && hipMemset(n.w, 0, sizeof(float) * n.P) == hipSuccess;
     ok = ok && hipMemset(n.m, 0, sizeof(float) * n.P) == hipSuccess;
