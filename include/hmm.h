@@ -87,7 +87,18 @@ typedef enum {
      * products are formed independently on the matrix cores (FP32 MFMA) with
      * the emissions computed in the same kernel, then the segment products are
      * combined by a tree of matrix products on the GPU.  O(T K^3) work.
-     * K <= 80. */
+     * K <= 80.
+     * With the default tuning knobs (hmm_ctx_set_blocking(ctx, 0, 0),
+     * hmm_ctx_set_packing(ctx, 1)) the segments are first walked by forward
+     * vectors, O(T K^2) work: each segment starts from a flat vector 32..160
+     * observations early, and on the device every segment's start is checked,
+     * entry by entry (relative 2^-16), against the end of the segment before
+     * it; segments that differ are run again from there.  Where the check is
+     * not met (chains that hardly forget), and where Gamma has an entry below
+     * 2^-56 (zeros included), the products above are computed in the same
+     * call.  Both give ln L within the same FP32 rounding.  Used for K > 25
+     * from T = 64, K > 16 from T = 1000, smaller K from T = 10^6 (K > 4) or 4 10^6, where
+     * it is the faster one. */
     HMM_BLOCKED_F32 = 1,
     /* The same plan with the segment products on 16-bit MFMA: the running
      * product and the emission-scaled transition matrix are rounded to bf16
@@ -287,8 +298,9 @@ int hmm_blocked_plan(hmm_ctx *ctx, int32_t K, int64_t T, int64_t *block_len,
                      int64_t *n_blocks, int32_t *levels);
 
 /* Kernel timing for measurement.  While enabled (on != 0), every blocked
- * call records a pair of HIP events on its stream around its segment-product
- * kernel (the dominant kernel of HMM_BLOCKED_*).  hmm_ctx_profile_read waits
+ * call records a pair of HIP events on its stream around the kernels that walk
+ * the observations (the segment chains where they are used, and the segment
+ * products, which return at once where the chains have served the call).  hmm_ctx_profile_read waits
  * for the recorded events, returns the number of timed launches and their
  * summed duration in milliseconds, and forgets them.  At most 65536 launches
  * are kept; later ones are not timed.  Enabling or disabling also forgets. */

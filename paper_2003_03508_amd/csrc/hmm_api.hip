@@ -162,6 +162,14 @@ void launch_serial(int KP, hipStream_t st, int K, int64_t T, const double *delta
     }
 }
 
+// The segment chains serve the FP32 blocked algorithm under the default
+// tuning knobs (set, the knobs ask for a plan of the product path).
+ChainPlan chain_plan(const hmm_ctx *ctx, int algo, int K, int64_t T)
+{
+    if (algo != HMM_BLOCKED_F32 || !ctx->default_plan()) return ChainPlan();
+    return make_chain_plan(K, T);
+}
+
 // Blocks of the Poisson log-factorial sum (partials live after the layout).
 constexpr int kFactBlocks = 1024;
 
@@ -187,7 +195,8 @@ int loglik_impl(hmm_ctx *ctx, int kind, int32_t K, const double *delta, const do
         int *status = at<int>(ctx->ws, ly.status);
         StateConst *sc = at<StateConst>(ctx->ws, ly.sc);
         float *gf = at<float>(ctx->ws, ly.gf);
-        hipLaunchKernelGGL(k_prepare, dim3(1), dim3(256), 0, st, kind, K, KP, delta, Gamma, a, b, c, sc, gf, status);
+        hipLaunchKernelGGL(k_prepare, dim3(1), dim3(256), 0, st, kind, K, KP, delta, Gamma, a, b, c, sc, gf, status,
+                           (int *)nullptr);
         if (kind == kEmisTremor)
             launch_serial<false>(KP, st, K, T, delta, gf, sc, obs, status, out);
         else
@@ -206,13 +215,15 @@ int loglik_impl(hmm_ctx *ctx, int kind, int32_t K, const double *delta, const do
     const int KP = ks.KP();
     Plan pl = make_plan(ctx, KP, T, ks.packG, ks.packWaves, ks.seg_waves());
     if (pl.n1 > INT_MAX || !grid_fits(pl.n1, 64 * pl.waves)) return HMM_E_UNSUPPORTED;
-    Layout ly = make_layout(KP, pl);
+    const ChainPlan cp = chain_plan(ctx, algo, K, T);
+    Layout ly = make_layout(KP, pl, cp);
     rc = ensure_ws(ctx, ly.total + sizeof(double) * kFactBlocks);
     if (rc != HMM_OK) return rc;
     int *status = at<int>(ctx->ws, ly.status);
     StateConst *sc = at<StateConst>(ctx->ws, ly.sc);
     float *gf = at<float>(ctx->ws, ly.gf);
-    hipLaunchKernelGGL(k_prepare, dim3(1), dim3(256), 0, st, kind, K, KP, delta, Gamma, a, b, c, sc, gf, status);
+    hipLaunchKernelGGL(k_prepare, dim3(1), dim3(256), 0, st, kind, K, KP, delta, Gamma, a, b, c, sc, gf, status,
+                       cp.nb > 0 ? at<int>(ctx->ws, ly.chain) : nullptr);
     SetDesc d;
     d.obs = obs;
     d.sc = sc;
@@ -224,7 +235,7 @@ int loglik_impl(hmm_ctx *ctx, int kind, int32_t K, const double *delta, const do
     d.L = pl.L;
     d.K = K;
     d.pad = 0;
-    rc = run_single(ctx, ctx->ws, ks, d, pl, ly, st);
+    rc = run_single(ctx, ctx->ws, ks, d, pl, ly, cp, st);
     if (rc != HMM_OK) return rc;
     if (kind == kEmisPoisson && T > 0) {
         hipLaunchKernelGGL(k_log_factorials, dim3(kFactBlocks), dim3(256), 0, st, T, obs.cnt,
@@ -267,7 +278,7 @@ int noalloc_scratch(int dev, void **ptr)
 
 // Bytes of scratch one tremor-model likelihood needs (default segment
 // lengths), or 0 if the request is not supported.
-size_t loglik_scratch_bytes(int32_t K, int64_t T, int32_t algo, KernelSet *ks, Plan *pl, Layout *ly)
+size_t loglik_scratch_bytes(int32_t K, int64_t T, int32_t algo, KernelSet *ks, Plan *pl, Layout *ly, ChainPlan *cp)
 {
     const hmm_ctx defaults;
     if (algo == HMM_SERIAL_F32) {
@@ -277,7 +288,8 @@ size_t loglik_scratch_bytes(int32_t K, int64_t T, int32_t algo, KernelSet *ks, P
     if (!select_kernels(algo, K, ks, defaults.packing)) return 0;
     *pl = make_plan(&defaults, ks->KP(), T, ks->packG, ks->packWaves, ks->seg_waves());
     if (pl->n1 > INT_MAX || !grid_fits(pl->n1, 64 * pl->waves)) return 0;
-    *ly = make_layout(ks->KP(), *pl);
+    *cp = chain_plan(&defaults, algo, K, T);
+    *ly = make_layout(ks->KP(), *pl, *cp);
     return ly->total;
 }
 
@@ -403,7 +415,8 @@ int hmm_loglik_noalloc(int32_t K, const double *delta, const double *Gamma, cons
     KernelSet ks;
     Plan pl;
     Layout ly;
-    const size_t need = loglik_scratch_bytes(K, T, algo, &ks, &pl, &ly);
+    ChainPlan cp;
+    const size_t need = loglik_scratch_bytes(K, T, algo, &ks, &pl, &ly, &cp);
     if (need == 0) return HMM_E_UNSUPPORTED;
     if (need > kNoAllocScratchBytes) return HMM_E_UNSUPPORTED;
     int dev = 0;
@@ -422,12 +435,12 @@ int hmm_loglik_noalloc(int32_t K, const double *delta, const double *Gamma, cons
     if (algo == HMM_SERIAL_F32) {
         const int KP = serial_kp(K);
         hipLaunchKernelGGL(k_prepare, dim3(1), dim3(256), 0, st, kEmisTremor, K, KP, delta, Gamma, p, mu, Sigma,
-                           sc, gf, status);
+                           sc, gf, status, (int *)nullptr);
         launch_serial<false>(KP, st, K, T, delta, gf, sc, obs, status, out);
         return launch_status();
     }
     hipLaunchKernelGGL(k_prepare, dim3(1), dim3(256), 0, st, kEmisTremor, K, ks.KP(), delta, Gamma, p, mu, Sigma,
-                       sc, gf, status);
+                       sc, gf, status, cp.nb > 0 ? at<int>(ws, ly.chain) : nullptr);
     SetDesc d;
     d.obs = obs;
     d.sc = sc;
@@ -439,7 +452,7 @@ int hmm_loglik_noalloc(int32_t K, const double *delta, const double *Gamma, cons
     d.L = pl.L;
     d.K = K;
     d.pad = 0;
-    rc = run_single(nullptr, ws, ks, d, pl, ly, st);
+    rc = run_single(nullptr, ws, ks, d, pl, ly, cp, st);
     if (rc != HMM_OK) return rc;
     return launch_status();
 }

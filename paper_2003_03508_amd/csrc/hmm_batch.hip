@@ -378,6 +378,7 @@ int build(hmm_ctx *ctx, BatchPlan &bp)
         pj.sc = reinterpret_cast<StateConst *>(base + o_sc[s]);
         pj.GF = reinterpret_cast<float *>(base + o_gf[s]);
         pj.status = status + s;
+        pj.chain = nullptr;
         pj.K = bp.K[s];
         pj.KP = kp[s];
     }
@@ -421,8 +422,7 @@ int enqueue_class(const BatchPlan &bp, const BatchClass &c, hipStream_t st)
                    ? HMM_OK
                    : HMM_E_DEVICE;
     }
-    SetDesc none;
-    std::memset(&none, 0, sizeof(none));
+    SetDesc none{};
     const size_t rb = (size_t)region_bytes(c.ks.KP());
     if (c.njobs > 0 &&
         launch_seg(c.seg, (unsigned)(c.grid > 0 ? c.grid : (int64_t)c.njobs), c.waves, c.seg_lds, st, none, bp.sets,

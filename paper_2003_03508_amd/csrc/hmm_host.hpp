@@ -15,6 +15,7 @@
 
 #include "../../include/hmm.h"
 #include "hmm_kernels.hpp"
+#include "hmm_chain.hpp"
 
 namespace hmmh {
 struct BatchPlan;                  // hmm_batch.hip
@@ -43,6 +44,10 @@ struct hmm_ctx {
     // FP32 paths with 16 < K <= 28: segments per wavefront packed into column
     // tiles (0 off, 1 the per-K default, 2, 4 or 5 tiles where built)
     int packing = 1;
+    // measurement of product-path candidates: no segment chains
+    bool no_chain = false;
+    // the tuning knobs ask for a plan of the product path
+    bool default_plan() const { return block_len == 0 && fold == 0 && packing == 1 && !no_chain; }
 };
 
 namespace hmmh {
@@ -189,12 +194,53 @@ inline Plan make_plan(const hmm_ctx *ctx, int KP, int64_t T, int packG = 0, int 
     return p;
 }
 
+// Segment chains of one set: segments, workgroups and walkers (wavefronts) of
+// k_chain.  One workgroup (64 segments) per CU, but no segment shorter than
+// kChainMinLen: the warm-up is repeated for every segment, so below that the
+// segments only add work (and a rerun extends the warm-up by one segment).
+// At most kChainMaxLen: a pair addresses its 16 segments by 32-bit offsets.
+constexpr int64_t kChainMinLen = 32, kChainMaxLen = int64_t(1) << 22;
+
+// Shortest sequence the segment chains are tried on.  They replace K^3 by K^2
+// work but cost two launches more (about 5 us each) and a warm-up of 32..160
+// dependent steps, so with few states the product path is faster until its
+// work outgrows them (whole hmm_loglik call, product path / chains, us):
+//   K = 3   T = 1e5 30 / 55,   1e6 78 / 64      K = 16  T = 1e5 53 / 70,  1e6 168 / 78
+//   K = 20  T = 200 57 / 68,  1000 88 / 77      K = 25  T = 1e6 458 / 121
+//   K = 33  T = 200 148 / 81,  1e6 1488 / 131   K = 80  T = 200 344 / 170, 1e6 8174 / 273
+inline int64_t chain_min_T(int K)
+{
+    return K <= 4 ? 4000000 : (K <= 16 ? 1000000 : (K <= 25 ? 1000 : 64));
+}
+
+struct ChainPlan {
+    int64_t nb = 0, q = 0, r = 0, wgs = 0, waves = 0;
+};
+
+inline ChainPlan make_chain_plan(int K, int64_t T, int64_t target_segs = 256 * kChainSegsPerWg)
+{
+    ChainPlan c;
+    if (T < chain_min_T(K)) return c;
+    const int64_t L = std::min(kChainMaxLen, std::max<int64_t>(kChainMinLen, (T + target_segs - 1) / target_segs));
+    c.nb = (T + L - 1) / L;
+    c.q = T / c.nb;
+    c.r = T % c.nb;
+    c.waves = (c.nb + kChainCols - 1) / kChainCols;
+    c.wgs = (c.nb + kChainSegsPerWg - 1) / kChainSegsPerWg;
+    return c;
+}
+
+// k_chain for K states (any emission kind with gen); compiled in
+// hmm_chain.hip.
+const void *chain_kernel(int K, bool gen);
+
 struct Layout {
+    size_t chain = 0, vs = 0, ve = 0, part = 0;
     size_t status = 0, sc = 0, gf = 0, m0 = 0, e0 = 0, s0 = 0, m1 = 0, e1 = 0, s1 = 0, m2 = 0,
            e2 = 0, s2 = 0, total = 0;
 };
 
-inline Layout make_layout(int KP, const Plan &pl)
+inline Layout make_layout(int KP, const Plan &pl, const ChainPlan &cp = ChainPlan())
 {
     Layout l;
     size_t off = 0;
@@ -219,6 +265,12 @@ inline Layout make_layout(int KP, const Plan &pl)
     l.m2 = take(sizeof(float) * KP * KP * n2);
     l.e2 = take(sizeof(long long) * KP * n2);
     l.s2 = take(sizeof(long long) * n2);
+    if (cp.nb > 0) {
+        l.chain = take(sizeof(int) * kChainWords);
+        l.vs = take(sizeof(float) * KP * cp.waves);
+        l.ve = take(sizeof(float) * KP * cp.waves);
+        l.part = take(sizeof(double) * cp.waves);
+    }
     l.total = off;
     return l;
 }
@@ -395,11 +447,39 @@ inline hipError_t launch_fold(const void *fn, unsigned grid, int W2, size_t lds,
     return hipLaunchKernel(fn, dim3(grid), dim3(64 * W2), args, lds, st);
 }
 
-// Single-set blocked path after parameter preparation: segment kernel, then
+// Puts the chain state of a set (layout ly at ws) into its descriptor.
+inline void set_chain(SetDesc *d, void *ws, const Layout &ly, const ChainPlan &cp)
+{
+    d->fail = at<int>(ws, ly.chain);
+    d->warm = at<int>(ws, ly.chain) + 1;
+    d->vs = at<float>(ws, ly.vs);
+    d->ve = at<float>(ws, ly.ve);
+    d->part = at<double>(ws, ly.part);
+    d->cnb = cp.nb;
+    d->cq = cp.q;
+    d->cr = cp.r;
+}
+
+// The two launches of the segment chains: the chains, then the check across
+// walkers (nothing to check with one walker).
+inline hipError_t launch_chain(const void *fn, unsigned grid, size_t lds, hipStream_t st, SetDesc one,
+                               const SetDesc *sets, const ChainJob *jobs, bool check)
+{
+    for (int mode = 0; mode < (check ? 2 : 1); ++mode) {
+        void *args[] = {&one, &sets, &jobs, &mode};
+        const hipError_t e = hipLaunchKernel(fn, dim3(grid), dim3(128 * kChainPairs), args, lds, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// Single-set blocked path after parameter preparation: the segment chains
+// where the plan has them, and (returning at once where those served the
+// set) the product path: segment kernel, then
 // fold levels (m0 -> m1 -> m2 -> m1 -> ...) until one workgroup finishes ln L.
 // ws holds the layout ly; ctx (may be null) only supplies the timing events.
 inline int run_single(hmm_ctx *ctx, void *ws, const KernelSet &ks, SetDesc d, const Plan &pl, const Layout &ly,
-                      hipStream_t st)
+                      const ChainPlan &cp, hipStream_t st)
 {
     const int KP = ks.KP();
     const bool packed = pl.packed;
@@ -422,7 +502,15 @@ inline int run_single(hmm_ctx *ctx, void *ws, const KernelSet &ks, SetDesc d, co
         ev1 = ctx->events[ctx->events_used].second;
         ++ctx->events_used;
     }
+    const void *chain = cp.nb > 0 ? chain_kernel(d.K, !tremor) : nullptr;
+    if (chain) {
+        if (allow_lds(chain, chain_lds_bytes(d.K)) != HMM_OK) return HMM_E_DEVICE;
+        set_chain(&d, ws, ly, cp);
+    }
     if (ev0) (void)hipEventRecord(ev0, st);
+    if (chain && launch_chain(chain, (unsigned)cp.wgs, chain_lds_bytes(d.K), st, d, nullptr, nullptr,
+                              cp.waves > 1) != hipSuccess)
+        return HMM_E_DEVICE;
     if (pl.nb > 0) {
         if (launch_seg(seg, (unsigned)pl.n1, pl.waves, seg_lds, st, d, nullptr, nullptr, pl.nb,
                        at<float>(ws, ly.m0), at<long long>(ws, ly.e0), at<long long>(ws, ly.s0)) != hipSuccess)

@@ -82,6 +82,74 @@ __device__ __forceinline__ int prepare_state_kind(int kind, int k, int K, const 
     return bad;
 }
 
+// Words of a set's chain state (k_chain), written by the preparation:
+// [0] fail: nonzero where the segment chains cannot serve the set,
+// [1] warm: warm-up steps of its segments.
+constexpr int kChainWords = 2;
+
+// Whether a transition matrix suits the segment chains, and their warm-up.
+// Usable: every entry is at least kChainMinGamma.  A chain vector's entries
+// below 2^-126 are flushed while its largest stays above 2^-40 (checked,
+// kChainLow), so a flushed entry is below 2^-86 of it and one step later
+// contributes less than 2^-86 / 2^-56 = 2^-30 of every entry of the vector:
+// less than FP32 rounding, whatever the observations.
+// Warm-up: the chain forgets at least about as fast as a state is left when
+// the observations say nothing, so 16 / -ln(max_i Gamma_ii) steps (e^-16 is
+// below the tolerance 2^-16 of the check), within 32..160.  Tremor data at
+// K = 8..80 needed 16..96 steps; what a warm-up misses costs a rerun of the
+// segments (max_i Gamma_ii near 1 with informative data converges long before
+// the bound), never the result.
+constexpr float kChainMinGamma = 0x1p-56f;
+
+__device__ __forceinline__ int chain_warmup(float dmax)
+{
+    if (!(dmax < 1.f)) return 160;
+    const float w = 4.f * ceilf(4.f / -logf(fmaxf(dmax, 1e-3f)));
+    return (int)fminf(fmaxf(w, 32.f), 160.f);
+}
+
+// Gamma in FP32, zero-padded to KP x KP (pitch KP), its checks, and (chain)
+// its smallest entry and largest diagonal entry in the LDS words red[0] and
+// red[1], which thread 0 sets to {FP32 +inf bits, 0} before a barrier.
+// Returns 1 for an invalid entry.
+__device__ __forceinline__ int prepare_gamma(int K, int KP, const double *__restrict__ Gamma, float *__restrict__ GF,
+                                             bool chain, unsigned *red)
+{
+    int bad = 0;
+    float gmin = __builtin_inff(), dmax = 0.f;
+    for (int idx = threadIdx.x; idx < KP * KP; idx += blockDim.x) {
+        const int i = idx / KP, j = idx % KP;
+        float v = 0.f;
+        if (i < K && j < K) {
+            const double gij = Gamma[(int64_t)i * K + j];
+            if (!(isfinite(gij) && gij >= 0.0 && gij <= 1.0)) bad = 1;
+            v = (float)gij;
+            gmin = fminf(gmin, v);
+            if (i == j) dmax = fmaxf(dmax, v);
+        }
+        GF[idx] = v;
+    }
+    if (!chain) return bad;
+    // entries in [0, 1]: bit patterns order like the values (with an invalid
+    // one the words are not used); one LDS atomic per wavefront
+    unsigned lo = __float_as_uint(gmin), hi = __float_as_uint(dmax);
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = min(lo, (unsigned)__shfl_xor((int)lo, o));
+        hi = max(hi, (unsigned)__shfl_xor((int)hi, o));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        atomicMin(&red[0], lo);
+        atomicMax(&red[1], hi);
+    }
+    return bad;
+}
+
+__device__ __forceinline__ void write_chain_words(const unsigned *red, int *chain)
+{
+    chain[0] = __uint_as_float(red[0]) >= kChainMinGamma ? 0 : 1;
+    chain[1] = chain_warmup(__uint_as_float(red[1]));
+}
+
 // kind: kEmisTremor (p, mu, Sigma as in eq. 1) or another kind (p = e0,
 // mu = e1, Sigma unused).
 static __global__ __launch_bounds__(256) void k_prepare(int kind, int K, int KP, const double *__restrict__ delta,
@@ -90,10 +158,16 @@ static __global__ __launch_bounds__(256) void k_prepare(int kind, int K, int KP,
                                                  const double *__restrict__ mu,
                                                  const double *__restrict__ Sigma,
                                                  StateConst *__restrict__ sc,
-                                                 float *__restrict__ GF, int *__restrict__ status)
+                                                 float *__restrict__ GF, int *__restrict__ status,
+                                                 int *__restrict__ chain)
 {
     __shared__ int bad;
-    if (threadIdx.x == 0) bad = 0;
+    __shared__ unsigned red[2];
+    if (threadIdx.x == 0) {
+        bad = 0;
+        red[0] = 0x7f800000u;
+        red[1] = 0u;
+    }
     __syncthreads();
     int mybad = 0;
     for (int k = threadIdx.x; k < KP; k += blockDim.x) {
@@ -101,19 +175,13 @@ static __global__ __launch_bounds__(256) void k_prepare(int kind, int K, int KP,
                                        : prepare_state_kind(kind, k, K, p, mu, sc);
         if (k < K && !(isfinite(delta[k]) && delta[k] >= 0.0)) mybad = 1;
     }
-    for (int idx = threadIdx.x; idx < KP * KP; idx += blockDim.x) {
-        const int i = idx / KP, j = idx % KP;
-        float v = 0.f;
-        if (i < K && j < K) {
-            const double gij = Gamma[(int64_t)i * K + j];
-            if (!(isfinite(gij) && gij >= 0.0 && gij <= 1.0)) mybad = 1;
-            v = (float)gij;
-        }
-        GF[idx] = v;
-    }
+    mybad |= prepare_gamma(K, KP, Gamma, GF, chain != nullptr, red);
     if (mybad) atomicOr(&bad, 1);
     __syncthreads();
-    if (threadIdx.x == 0) *status = bad ? kBadParams : 0;
+    if (threadIdx.x == 0) {
+        *status = bad ? kBadParams : 0;
+        if (chain) write_chain_words(red, chain);
+    }
 }
 
 // Batched preparation: workgroup s prepares set s from its packed FP64
@@ -123,6 +191,7 @@ struct PrepJob {
     StateConst *sc;
     float *GF;
     int *status;
+    int *chain;   // kChainWords words, or null
     int K, KP;
 };
 
@@ -133,26 +202,25 @@ static __global__ __launch_bounds__(256) void k_prepare_batch(const PrepJob *__r
     const double *delta = j.params, *Gamma = delta + K, *p = Gamma + (int64_t)K * K, *mu = p + K,
                  *Sigma = mu + 2 * K;
     __shared__ int bad;
-    if (threadIdx.x == 0) bad = 0;
+    __shared__ unsigned red[2];
+    if (threadIdx.x == 0) {
+        bad = 0;
+        red[0] = 0x7f800000u;
+        red[1] = 0u;
+    }
     __syncthreads();
     int mybad = 0;
     for (int k = threadIdx.x; k < KP; k += blockDim.x) {
         mybad |= prepare_state(k, K, p, mu, Sigma, j.sc);
         if (k < K && !(isfinite(delta[k]) && delta[k] >= 0.0)) mybad = 1;
     }
-    for (int idx = threadIdx.x; idx < KP * KP; idx += blockDim.x) {
-        const int i = idx / KP, jj = idx % KP;
-        float v = 0.f;
-        if (i < K && jj < K) {
-            const double gij = Gamma[(int64_t)i * K + jj];
-            if (!(isfinite(gij) && gij >= 0.0 && gij <= 1.0)) mybad = 1;
-            v = (float)gij;
-        }
-        j.GF[idx] = v;
-    }
+    mybad |= prepare_gamma(K, KP, Gamma, j.GF, j.chain != nullptr, red);
     if (mybad) atomicOr(&bad, 1);
     __syncthreads();
-    if (threadIdx.x == 0) *j.status = bad ? kBadParams : 0;
+    if (threadIdx.x == 0) {
+        *j.status = bad ? kBadParams : 0;
+        if (j.chain) write_chain_words(red, j.chain);
+    }
 }
 
 // The state part of k_prepare alone (emission parameters only).
@@ -375,7 +443,25 @@ struct SetDesc {
     double *out;             // the set's ln L
     int64_t T, L;            // observations, segment length
     int K, pad;
+    // segment chains (k_chain); fail null: the set has none.  Where *fail is 0
+    // after them, the segment and fold kernels of the product path return at
+    // once and the final one adds up part.
+    int *fail = nullptr;
+    const int *warm = nullptr;
+    float *vs = nullptr, *ve = nullptr;   // [waves][KP]: start of each walker's first segment, end of its last
+    double *part = nullptr;               // [waves] sums of ln ratios
+    int64_t cnb = 0, cq = 0, cr = 0;      // segments of cq or (the first cr of them) cq + 1 observations
+
+    // the segment chains have served the set
+    __device__ __forceinline__ bool chained() const { return fail && *fail == 0; }
 };
+// Segment-chain work item of a batch: workgroup wg of one set.
+struct ChainJob {
+    int64_t wg;
+    int set, pad;
+};
+// Segments per workgroup of k_chain (4 walkers of 16).
+constexpr int kChainSegsPerWg = 64;
 // Segment-kernel work item of a batch: segments [seg0, seg0 + nseg) of one set,
 // product written to slot `out`.
 struct WgJob {
@@ -841,9 +927,11 @@ __global__ __launch_bounds__(64 * group_waves(S * MT)) void k_blocked(SetDesc on
     if constexpr (BATCH) {
         run_jobs(jobs, nb, queue, [&](const WgJob &job, int salt) {
             const SetDesc d = sets[job.set];
+            if (d.chained()) return;
             blocked_job<S, MT, NSL, GEN>(d, job, Mout, Eout, Sout, salt);
         });
     } else {
+        if (one.chained()) return;
         const int W = blockDim.x >> 6;
         WgJob job;
         job.seg0 = (int64_t)blockIdx.x * W;
@@ -1136,9 +1224,11 @@ __global__ __launch_bounds__(64 * pack_waves<NT>()) void k_blocked_packed(SetDes
     if constexpr (BATCH) {
         run_jobs(jobs, nb, queue, [&](const WgJob &job, int salt) {
             const SetDesc d = sets[job.set];
+            if (d.chained()) return;
             packed_job<NT, G, NSL>(d, job, Mout, Eout, Sout, salt);
         });
     } else {
+        if (one.chained()) return;
         const int W = (blockDim.x >> 6) * G;
         WgJob job;
         job.seg0 = (int64_t)blockIdx.x * W;
@@ -1162,6 +1252,7 @@ __global__ __launch_bounds__(64 * pack_waves<NT>()) void k_blocked_packed_kind(S
     (void)sets;
     (void)jobs;
     (void)queue;
+    if (one.chained()) return;
     const int W = (blockDim.x >> 6) * G;
     WgJob job;
     job.seg0 = (int64_t)blockIdx.x * W;
@@ -1461,6 +1552,31 @@ __global__ __launch_bounds__(64 * lp_waves<MT>()) void k_blocked_lp(SetDesc one,
     }
 }
 
+// ln L of a set that the segment chains have served: ln sum(delta) plus the
+// walkers' sums, added in a fixed order (thread i takes i, i + blockDim, ...,
+// then a tree in LDS).  One workgroup.
+__device__ __forceinline__ void chain_finish(const SetDesc &d, float *smem)
+{
+    double *red = reinterpret_cast<double *>(smem);
+    const int64_t n = (d.cnb + 15) / 16;
+    double s = 0.0;
+    for (int64_t i = threadIdx.x; i < n; i += blockDim.x) s += d.part[i];
+    red[threadIdx.x] = s;
+    double t = 0.0;
+    if (threadIdx.x < 64)
+        for (int k = threadIdx.x; k < d.K; k += 64) t += d.delta[k];
+    t = wave_sum_f64(t);
+    __syncthreads();
+    int m = blockDim.x;
+    while (m > 1) {
+        const int h = (m + 1) / 2;
+        if ((int)threadIdx.x + h < m) red[threadIdx.x] += red[threadIdx.x + h];
+        __syncthreads();
+        m = h;
+    }
+    if (threadIdx.x == 0) *d.out = *d.status ? __builtin_nan("") : log(t) + red[0];
+}
+
 // ---------------------------------------------------------------------------
 // Combination of products: workgroup q of W wavefronts takes inputs
 // [q*F*W, (q+1)*F*W); wave w folds its F consecutive inputs left to right
@@ -1502,6 +1618,10 @@ __global__ __launch_bounds__(64 * group_waves(S * MT)) void k_fold(SetDesc one, 
         job.set = 0;
     }
     const int K = d.K;
+    if (d.chained()) {
+        if (job.final_) chain_finish(d, smem);
+        return;
+    }
 
     Prod<S, MT> P;
     long long ssum = 0;

@@ -858,7 +858,7 @@ int viterbi_impl(hmm_ctx *ctx, int32_t K, const double *delta, const double *Gam
     int *status = at<int>(ws, o_status);
     StateConst *sc = at<StateConst>(ws, o_sc);
     hipLaunchKernelGGL(k_prepare, dim3(1), dim3(256), 0, st, (int)kEmisTremor, K, KB, delta, Gamma, p, mu, Sigma, sc,
-                       at<float>(ws, o_gf), status);
+                       at<float>(ws, o_gf), status, (int *)nullptr);
     VitDesc d;
     d.flag = flag;
     d.xy = xy;
