@@ -90,7 +90,7 @@ typedef enum {
      * K <= 80.
      * With the default tuning knobs (hmm_ctx_set_blocking(ctx, 0, 0),
      * hmm_ctx_set_packing(ctx, 1)) the segments are first walked by forward
-     * vectors, O(T K^2) work: each segment starts from a flat vector 32..160
+     * vectors, O(T K^2) work: each segment starts from a flat vector 40..112
      * observations early, and on the device every segment's start is checked,
      * entry by entry (relative 2^-16), against the end of the segment before
      * it; segments that differ are run again from there.  Where the check is

@@ -11,6 +11,7 @@ LIB = os.path.join(HERE, "libhmm.so")
 UNITS = [(os.path.join(CSRC, "hmm_api.hip"), ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]),
          (os.path.join(CSRC, "hmm_large.hip"), []),
          (os.path.join(CSRC, "hmm_chain.hip"), ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]),
+         (os.path.join(CSRC, "hmm_chain_kinds.hip"), ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]),
          (os.path.join(CSRC, "hmm_batch.hip"), []),
          (os.path.join(CSRC, "hmm_sampler.hip"), []),
          (os.path.join(CSRC, "hmm_posterior.hip"), []),

@@ -24,7 +24,6 @@
 
 namespace hmm {
 
-constexpr int kChainPairs = 4;     // pairs of wavefronts per workgroup
 constexpr int kChainCols = 16;     // segments per pair (columns of an MFMA tile)
 constexpr int kChainStep = 4;      // steps per staged chunk: 16 x 4 observations = 64 lanes
 constexpr int kChainRepairs = 3;   // reruns of segments from their neighbours' ends
@@ -82,11 +81,28 @@ __device__ __forceinline__ bool chain_parallel(float s, float e, float ss, float
 
 static_assert(sizeof(StateConst) == 64, "k_chain reads the constants as 8 doubles per state");
 
-// LDS of one workgroup: two buffers of 4 ceil(K / 4) x 64 staged emissions per
-// pair (160 KiB at K = 80); the few words exchanged between passes reuse it.
-__host__ __device__ constexpr int chain_lds_bytes(int K)
+// Workgroup shapes of k_chain: NP walkers with NS stagers each.  A stager's
+// VALU work and a walker's matrix work do not overlap on one SIMD (measured:
+// they add up), so a wavefront per SIMD is the best use of a CU while the
+// segments allow it, and fewer, longer segments repeat less warm-up.
+//  K <= 32: the stager is the longer of the two.  Short sequences take one
+//    walker with two stagers (the latency of a step decides), longer ones two
+//    pairs.
+//  K > 32: two pairs, and for long sequences four (two wavefronts per SIMD:
+//    15 % more throughput at K = 80, where the walker is the longer one).
+struct ChainShape {
+    int NP, NS;
+    int64_t segs() const { return 16 * (int64_t)NP; }
+    int threads() const { return 64 * NP * (1 + NS); }
+    // two buffers of 4 ceil(K / 4) x 64 staged emissions per walker (160 KiB
+    // at K = 80 and four walkers); the words exchanged between passes reuse it
+    size_t lds(int K) const { return (size_t)NP * 2 * ((K + 3) / 4 * 4) * 64 * 4; }
+};
+
+inline ChainShape chain_shape(int K, bool big)
 {
-    return kChainPairs * 2 * ((K + 3) / 4 * 4) * 64 * 4;
+    if (K <= 32) return big ? ChainShape{2, 1} : ChainShape{1, 2};
+    return big ? ChainShape{4, 1} : ChainShape{2, 1};
 }
 
 // Larger of two numbers in one instruction (fmax also quiets NaNs, in two).
@@ -271,25 +287,29 @@ __device__ __forceinline__ void chain_segment(const SetDesc &d, int64_t b, int64
     }
 }
 
-template <int NSL, bool GEN, bool REGS = (NSL <= kStagerSlots)>
+// NS stagers share a walker's chunk by its steps (the second layout: NS = 1).
+template <int NSL, bool GEN, int NS, bool REGS = (NSL <= kStagerSlots)>
 struct ChainStager;
 
-template <int NSL, bool GEN>
-struct ChainStager<NSL, GEN, true> {
+template <int NSL, bool GEN, int NS>
+struct ChainStager<NSL, GEN, NS, true> {
+    static constexpr int NU = kChainStep / NS;   // steps of a chunk this stager evaluates
+
     // observations of the next D chunks, in flight: a chunk takes about
     // 0.3 us + 0.1 us per slot, a load from HBM 1 us or more
     static constexpr int D = NSL <= 4 ? 4 : 2;
     ObsWindow<GEN> win;
     int off, lo, n;          // segment's first observation in the window; live: (unsigned)(rel - lo) < n
-    int c, g, bad;
+    int c, g, u0, bad;
     long long ssum;          // shifts of the segment (the same on the four lanes of a segment)
     double cst[NSL][8];
-    RawObs raw[D][kChainStep];
+    RawObs raw[D][NU];
     int words[D];
 
-    __device__ __forceinline__ void init(const SetDesc &d, int64_t b0, int64_t base, int W, int lane)
+    __device__ __forceinline__ void init(const SetDesc &d, int64_t b0, int64_t base, int W, int lane, int part)
     {
         win.init(d.obs, base, d.T);
+        u0 = part * NU;
         c = lane & 15;
         g = lane >> 4;
         chain_segment(d, b0 + c, base, W, off, lo, n);
@@ -304,7 +324,7 @@ struct ChainStager<NSL, GEN, true> {
     {
         words[slot] = win.flag_word(off + rel);
 #pragma unroll
-        for (int u = 0; u < kChainStep; ++u) raw[slot][u] = win.value(off + rel + u);
+        for (int u = 0; u < NU; ++u) raw[slot][u] = win.value(off + rel + u0 + u);
     }
     __device__ __forceinline__ bool counts() const { return g == 0; }
     // the first chunk of a pass starts at step rel
@@ -319,18 +339,18 @@ struct ChainStager<NSL, GEN, true> {
     // wait for it)
     __device__ __forceinline__ void stage(int rel, float *E, int slot)
     {
-        RawObs now[kChainStep];
+        RawObs now[NU];
         const int word = words[slot];
 #pragma unroll
-        for (int u = 0; u < kChainStep; ++u) now[u] = raw[slot][u];
+        for (int u = 0; u < NU; ++u) now[u] = raw[slot][u];
         fetch(rel + D * kChainStep, slot);
-        float ev[NSL][kChainStep];
+        float ev[NSL][NU];
         int part = 0;
 #pragma unroll
-        for (int u = 0; u < kChainStep; ++u) {
+        for (int u = 0; u < NU; ++u) {
             int mask = -1;
-            const bool live = (unsigned)(rel + u - lo) < (unsigned)n;
-            if (!GEN) now[u].f = win.flag_of(word, off + rel, u);
+            const bool live = (unsigned)(rel + u0 + u - lo) < (unsigned)n;
+            if (!GEN) now[u].f = win.flag_of(word, off + rel, u0 + u);
             chain_check_obs<GEN>(win.kind, live, now[u], mask, bad);
             double lam[NSL];
             double m = -INFINITY;
@@ -356,14 +376,15 @@ struct ChainStager<NSL, GEN, true> {
         if (rel >= 0) ssum += part;
 #pragma unroll
         for (int j = 0; j < NSL; ++j) {
-            const float4 v = {ev[j][0], ev[j][1], ev[j][2], ev[j][3]};
-            *reinterpret_cast<float4 *>(E + (4 * j + g) * 64 + 4 * c) = v;
+            float *dst = E + (4 * j + g) * 64 + 4 * c + u0;
+            if constexpr (NU == 4) *reinterpret_cast<float4 *>(dst) = float4{ev[j][0], ev[j][1], ev[j][2], ev[j][3]};
+            else *reinterpret_cast<float2 *>(dst) = float2{ev[j][0], ev[j][1]};
         }
     }
 };
 
 template <int NSL, bool GEN>
-struct ChainStager<NSL, GEN, false> {
+struct ChainStager<NSL, GEN, 1, false> {
     typedef double d8 __attribute__((ext_vector_type(8)));
     static constexpr int D = 2;
     ObsWindow<GEN> win;
@@ -374,7 +395,7 @@ struct ChainStager<NSL, GEN, false> {
     RawObs raw[D];
     int words[D];
 
-    __device__ __forceinline__ void init(const SetDesc &d, int64_t b0, int64_t base, int W, int lane_)
+    __device__ __forceinline__ void init(const SetDesc &d, int64_t b0, int64_t base, int W, int lane_, int)
     {
         win.init(d.obs, base, d.T);
         lane = lane_;
@@ -444,13 +465,10 @@ struct ChainStager<NSL, GEN, false> {
 };
 
 // ---------------------------------------------------------------------------
-// Workgroup = kChainPairs pairs of wavefronts.  Wavefront p < 4 (the walker)
-// advances the vectors of 16 consecutive segments on the matrix cores; its
-// partner p + 4 (the stager, on the same SIMD) evaluates the emissions of the
-// next four steps of those segments meanwhile, one (segment, step) per lane,
-// into the other half of an LDS double buffer.  So the FP64 emission stage
-// (VALU) and the products (matrix cores) of one SIMD overlap; with one
-// wavefront doing both they add up.
+// Workgroup = NP walkers, then NP * NS stagers (ChainShape).  Walker p advances
+// the vectors of 16 consecutive segments on the matrix cores; its stagers
+// evaluate the emissions of the next four steps of those segments meanwhile,
+// into the other half of an LDS double buffer.
 //
 // mode 0: every segment; writes s of each walker's first segment (vs), e of
 //   its last (ve) and its sum of ln ratios (part).
@@ -459,9 +477,9 @@ struct ChainStager<NSL, GEN, false> {
 //   segments started from ve, requires that the ends stay the same, and
 //   replaces part.
 // ---------------------------------------------------------------------------
-template <int MT, int NSL, bool GEN>
-__global__ __launch_bounds__(128 * kChainPairs) void k_chain(SetDesc one, const SetDesc *__restrict__ sets,
-                                                             const ChainJob *__restrict__ jobs, int mode)
+template <int MT, int NSL, bool GEN, int NP, int NS>
+__global__ __launch_bounds__(64 * NP * (1 + NS)) void k_chain(SetDesc one, const SetDesc *__restrict__ sets,
+                                                              const ChainJob *__restrict__ jobs, int mode)
 {
     typedef Tile<16>::acc_t acc_t;
     extern __shared__ __attribute__((aligned(16))) float smem[];
@@ -475,14 +493,20 @@ __global__ __launch_bounds__(128 * kChainPairs) void k_chain(SetDesc one, const 
     int *ism = reinterpret_cast<int *>(smem);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int pair = wave & (kChainPairs - 1);
-    const bool walker = wave < kChainPairs;
+    const bool walker = wave < NP;
+    const int pair = walker ? wave : (wave - NP) % NP, share = walker ? 0 : (wave - NP) / NP;
     const int K = d.K;
-    const int64_t gw = scalar(wg * kChainPairs + pair);    // this pair among the set's
+    const int64_t gw = scalar(wg * NP + pair);   // this walker among the set's
     const int64_t b0 = gw * kChainCols;            // its first segment
     const int64_t nb = d.cnb, q = d.cq, qr = d.cr;
     const bool pair_live = b0 < nb;
 
+    auto verdicts = [&]() {   // of the workgroup's walkers, or'ed
+        int v = 0;
+#pragma unroll
+        for (int p = 0; p < NP; ++p) v |= ism[p];
+        return v;
+    };
     // one decision for the workgroup (the words may change while it runs)
     if (threadIdx.x == 0) ism[0] = (*d.fail != 0 || *d.status != 0) ? 1 : 0;
     chain_barrier();
@@ -508,7 +532,7 @@ __global__ __launch_bounds__(128 * kChainPairs) void k_chain(SetDesc one, const 
         }
         if (walker && lane == 0) ism[pair] = redo ? 1 : 0;
         chain_barrier();
-        const int any = ism[0] | ism[1] | ism[2] | ism[3];
+        const int any = verdicts();
         chain_barrier();
         if (!any) return;
     }
@@ -522,11 +546,11 @@ __global__ __launch_bounds__(128 * kChainPairs) void k_chain(SetDesc one, const 
 
     if (!walker) {
         // ------------------------------------------------------------ stager
-        ChainStager<NSL, GEN> sg;
-        constexpr int D = ChainStager<NSL, GEN>::D;
+        ChainStager<NSL, GEN, NS> sg;
+        constexpr int D = ChainStager<NSL, GEN, NS>::D;
         static_assert(D % 2 == 0, "chunk p of a run uses slot p % D and buffer p % 2");
         const int64_t t0 = pair_live ? packed_seg_start(b0, q, qr) : 0;
-        sg.init(d, b0, scalar(t0 > W ? t0 - W : (int64_t)0), W, lane);
+        sg.init(d, b0, scalar(t0 > W ? t0 - W : (int64_t)0), W, lane, share);
         for (int pass = 0;; ++pass) {
             const int rel0 = pass == 0 ? -W : 0;
             sg.start(rel0);
@@ -543,13 +567,13 @@ __global__ __launch_bounds__(128 * kChainPairs) void k_chain(SetDesc one, const 
                 }
             }
             chain_barrier();   // the walkers' verdicts are in LDS
-            const int any = ism[0] | ism[1] | ism[2] | ism[3];
+            const int any = verdicts();
             chain_barrier();
             if (any != 1 || pass == kChainRepairs) break;
         }
         if (__any(sg.bad) && lane == 0) atomicOr(d.status, kBadData);
         const long long ssum = wave_sum_i64(sg.counts() ? sg.ssum : 0);
-        if (lane == 0) reinterpret_cast<long long *>(smem)[8 + pair] = ssum;
+        if (lane == 0) reinterpret_cast<long long *>(smem)[8 + pair * NS + share] = ssum;
         chain_barrier();
         return;
     }
@@ -706,7 +730,7 @@ __global__ __launch_bounds__(128 * kChainPairs) void k_chain(SetDesc one, const 
         }
         if (lane == 0) ism[pair] = verdict;
         chain_barrier();
-        const int any = ism[0] | ism[1] | ism[2] | ism[3];
+        const int any = verdicts();
         chain_barrier();
         if (any != 1 || pass == kChainRepairs) break;
         // again from the first observation, each segment from its neighbour's end
@@ -727,7 +751,9 @@ __global__ __launch_bounds__(128 * kChainPairs) void k_chain(SetDesc one, const 
     part = wave_sum_f64(part);
     chain_barrier();   // the stagers' shift sums are in LDS
     if (!pair_live) return;
-    const long long stot = reinterpret_cast<const long long *>(smem)[8 + pair];
+    long long stot = 0;
+#pragma unroll
+    for (int k = 0; k < NS; ++k) stot += reinterpret_cast<const long long *>(smem)[8 + pair * NS + k];
     const global_ptr<float> vep = (global_ptr<float>)(d.ve + gw * KP);
     if (mode == 0) {
         if (c == 0) {

@@ -195,19 +195,24 @@ inline Plan make_plan(const hmm_ctx *ctx, int KP, int64_t T, int packG = 0, int 
 }
 
 // Segment chains of one set: segments, workgroups and walkers (wavefronts) of
-// k_chain.  One workgroup (64 segments) per CU, but no segment shorter than
-// kChainMinLen: the warm-up is repeated for every segment, so below that the
-// segments only add work (and a rerun extends the warm-up by one segment).
-// At most kChainMaxLen: a pair addresses its 16 segments by 32-bit offsets.
+// k_chain, and its workgroup shape.  One workgroup per CU, but no segment
+// shorter than kChainMinLen: the warm-up is repeated for every segment, so
+// below that the segments only add work (and a rerun extends the warm-up by
+// one segment).  At most kChainMaxLen: a walker's segments are addressed by
+// 32-bit offsets.
 constexpr int64_t kChainMinLen = 32, kChainMaxLen = int64_t(1) << 22;
+// From this many observations on the larger workgroup shape is used.
+inline int64_t chain_big_T(int K) { return K <= 32 ? 400000 : 1250000; }
 
 // Shortest sequence the segment chains are tried on.  They replace K^3 by K^2
-// work but cost two launches more (about 5 us each) and a warm-up of 32..160
+// work but cost two launches more (about 5 us each) and a warm-up of 40..112
 // dependent steps, so with few states the product path is faster until its
 // work outgrows them (whole hmm_loglik call, product path / chains, us):
-//   K = 3   T = 1e5 30 / 55,   1e6 78 / 64      K = 16  T = 1e5 53 / 70,  1e6 168 / 78
-//   K = 20  T = 200 57 / 68,  1000 88 / 77      K = 25  T = 1e6 458 / 121
-//   K = 33  T = 200 148 / 81,  1e6 1488 / 131   K = 80  T = 200 344 / 170, 1e6 8174 / 273
+//   K = 3   T = 1e5 30 / 55,   1e6 78 / 64      K = 16  T = 1e5 53 / 70,  1e6 165 / 80
+//   K = 20  T = 200 57 / 68,  1000 88 / 50      K = 25  T = 1e5 125 / 52, 1e6 458 / 90
+//   K = 33  T = 200 148 / 60,  1e6 1490 / 125   K = 80  T = 200 344 / 140, 1e6 8170 / 300
+// Few states also mix slowly as a rule, and a chain that is given back has
+// cost its attempt, so up to 16 states the line lies where that is small.
 inline int64_t chain_min_T(int K)
 {
     return K <= 4 ? 4000000 : (K <= 16 ? 1000000 : (K <= 25 ? 1000 : 64));
@@ -215,24 +220,35 @@ inline int64_t chain_min_T(int K)
 
 struct ChainPlan {
     int64_t nb = 0, q = 0, r = 0, wgs = 0, waves = 0;
+    bool big = false;
 };
 
-inline ChainPlan make_chain_plan(int K, int64_t T, int64_t target_segs = 256 * kChainSegsPerWg)
+// total: observations of all sets that share the launch (T for a single set).
+inline ChainPlan make_chain_plan(int K, int64_t T, int64_t total)
 {
     ChainPlan c;
-    if (T < chain_min_T(K)) return c;
-    const int64_t L = std::min(kChainMaxLen, std::max<int64_t>(kChainMinLen, (T + target_segs - 1) / target_segs));
+    if (T < 64) return c;
+    c.big = total >= chain_big_T(K);
+    const ChainShape sh = chain_shape(K, c.big);
+    const int64_t segs = 256 * sh.segs();
+    const int64_t L = std::min(kChainMaxLen, std::max<int64_t>(kChainMinLen, (total + segs - 1) / segs));
     c.nb = (T + L - 1) / L;
     c.q = T / c.nb;
     c.r = T % c.nb;
     c.waves = (c.nb + kChainCols - 1) / kChainCols;
-    c.wgs = (c.nb + kChainSegsPerWg - 1) / kChainSegsPerWg;
+    c.wgs = (c.nb + sh.segs() - 1) / sh.segs();
     return c;
 }
 
-// k_chain for K states (any emission kind with gen); compiled in
-// hmm_chain.hip.
-const void *chain_kernel(int K, bool gen);
+// k_chain by live contraction slots and workgroup shape (hmm_chain.hip,
+// hmm_chain_kinds.hip).
+const void *chain_kernel_tremor(int nsl, bool big);
+const void *chain_kernel_kinds(int nsl, bool big);
+
+inline const void *chain_kernel(int K, bool gen, bool big)
+{
+    return gen ? chain_kernel_kinds((K + 3) / 4, big) : chain_kernel_tremor((K + 3) / 4, big);
+}
 
 struct Layout {
     size_t chain = 0, vs = 0, ve = 0, part = 0;
@@ -462,12 +478,12 @@ inline void set_chain(SetDesc *d, void *ws, const Layout &ly, const ChainPlan &c
 
 // The two launches of the segment chains: the chains, then the check across
 // walkers (nothing to check with one walker).
-inline hipError_t launch_chain(const void *fn, unsigned grid, size_t lds, hipStream_t st, SetDesc one,
+inline hipError_t launch_chain(const void *fn, unsigned grid, int threads, size_t lds, hipStream_t st, SetDesc one,
                                const SetDesc *sets, const ChainJob *jobs, bool check)
 {
     for (int mode = 0; mode < (check ? 2 : 1); ++mode) {
         void *args[] = {&one, &sets, &jobs, &mode};
-        const hipError_t e = hipLaunchKernel(fn, dim3(grid), dim3(128 * kChainPairs), args, lds, st);
+        const hipError_t e = hipLaunchKernel(fn, dim3(grid), dim3(threads), args, lds, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -502,13 +518,14 @@ inline int run_single(hmm_ctx *ctx, void *ws, const KernelSet &ks, SetDesc d, co
         ev1 = ctx->events[ctx->events_used].second;
         ++ctx->events_used;
     }
-    const void *chain = cp.nb > 0 ? chain_kernel(d.K, !tremor) : nullptr;
+    const void *chain = cp.nb > 0 ? chain_kernel(d.K, !tremor, cp.big) : nullptr;
+    const ChainShape shape = chain_shape(d.K, cp.big);
     if (chain) {
-        if (allow_lds(chain, chain_lds_bytes(d.K)) != HMM_OK) return HMM_E_DEVICE;
+        if (allow_lds(chain, shape.lds(d.K)) != HMM_OK) return HMM_E_DEVICE;
         set_chain(&d, ws, ly, cp);
     }
     if (ev0) (void)hipEventRecord(ev0, st);
-    if (chain && launch_chain(chain, (unsigned)cp.wgs, chain_lds_bytes(d.K), st, d, nullptr, nullptr,
+    if (chain && launch_chain(chain, (unsigned)cp.wgs, shape.threads(), shape.lds(d.K), st, d, nullptr, nullptr,
                               cp.waves > 1) != hipSuccess)
         return HMM_E_DEVICE;
     if (pl.nb > 0) {

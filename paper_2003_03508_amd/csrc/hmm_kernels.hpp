@@ -93,19 +93,19 @@ constexpr int kChainWords = 2;
 // kChainLow), so a flushed entry is below 2^-86 of it and one step later
 // contributes less than 2^-86 / 2^-56 = 2^-30 of every entry of the vector:
 // less than FP32 rounding, whatever the observations.
-// Warm-up: the chain forgets at least about as fast as a state is left when
-// the observations say nothing, so 16 / -ln(max_i Gamma_ii) steps (e^-16 is
-// below the tolerance 2^-16 of the check), within 32..160.  Tremor data at
-// K = 8..80 needed 16..96 steps; what a warm-up misses costs a rerun of the
-// segments (max_i Gamma_ii near 1 with informative data converges long before
-// the bound), never the result.
+// Warm-up: the chain forgets about as fast as a state is left when the
+// observations say nothing, so 17 / -ln(max_i Gamma_ii) steps (e^-17, against
+// the tolerance 2^-16 = e^-11 of the check), within 40..112.  Tremor data at
+// K = 8..80 needed 32..96 steps.  What a warm-up misses costs a rerun of the
+// segments, never the result, but one rerun (32..512 steps) costs more than a
+// few steps of warm-up everywhere; past 112 the reruns carry on.
 constexpr float kChainMinGamma = 0x1p-56f;
 
 __device__ __forceinline__ int chain_warmup(float dmax)
 {
-    if (!(dmax < 1.f)) return 160;
-    const float w = 4.f * ceilf(4.f / -logf(fmaxf(dmax, 1e-3f)));
-    return (int)fminf(fmaxf(w, 32.f), 160.f);
+    if (!(dmax < 1.f)) return 112;
+    const float w = 4.f * ceilf(4.25f / -logf(fmaxf(dmax, 1e-3f)));
+    return (int)fminf(fmaxf(w, 40.f), 112.f);
 }
 
 // Gamma in FP32, zero-padded to KP x KP (pitch KP), its checks, and (chain)
@@ -460,8 +460,6 @@ struct ChainJob {
     int64_t wg;
     int set, pad;
 };
-// Segments per workgroup of k_chain (4 walkers of 16).
-constexpr int kChainSegsPerWg = 64;
 // Segment-kernel work item of a batch: segments [seg0, seg0 + nseg) of one set,
 // product written to slot `out`.
 struct WgJob {
