@@ -12,6 +12,7 @@ UNITS = [(os.path.join(CSRC, "hmm_api.hip"), ["-mllvm", "-amdgpu-mfma-vgpr-form=
          (os.path.join(CSRC, "hmm_large.hip"), []),
          (os.path.join(CSRC, "hmm_chain.hip"), ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]),
          (os.path.join(CSRC, "hmm_chain_kinds.hip"), ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]),
+         (os.path.join(CSRC, "hmm_chain_batch.hip"), ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]),
          (os.path.join(CSRC, "hmm_batch.hip"), []),
          (os.path.join(CSRC, "hmm_sampler.hip"), []),
          (os.path.join(CSRC, "hmm_posterior.hip"), []),

@@ -167,7 +167,7 @@ void launch_serial(int KP, hipStream_t st, int K, int64_t T, const double *delta
 ChainPlan chain_plan(const hmm_ctx *ctx, int algo, int K, int64_t T)
 {
     if (algo != HMM_BLOCKED_F32 || !ctx->default_plan() || T < chain_min_T(K)) return ChainPlan();
-    return make_chain_plan(K, T, T);
+    return make_chain_plan(K, T);
 }
 
 // Blocks of the Poisson log-factorial sum (partials live after the layout).

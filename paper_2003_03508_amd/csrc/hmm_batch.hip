@@ -50,6 +50,7 @@ struct BatchPlan {
     std::map<std::pair<int, int>, int> tunedW;
     bool persistent = true;
     int packing = 1;
+    bool chain = false;      // segment chains first (default tuning knobs, FP32)
     // device memory
     void *mem = nullptr;
     SetDesc *sets = nullptr;
@@ -57,7 +58,12 @@ struct BatchPlan {
     WgJob *jobs = nullptr;
     FoldJob *fjobs = nullptr;
     FoldJob *pjobs = nullptr;
-    int *queues = nullptr;   // one job counter per class, zeroed at the start of every launch sequence
+    // two words per class, zeroed at the start of every launch sequence: its
+    // job counter, and whether a set of it is left to the product path
+    int *queues = nullptr;
+    ChainJob *cjobs = nullptr;   // workgroups of the segment chains
+    size_t ncjobs = 0, chain_lds = 0;
+    int *cls = nullptr;          // class of every set
     std::vector<BatchClass> classes;
     // captured launch sequence (classes forked onto parallel branches)
     static constexpr int kBranches = 4;
@@ -149,12 +155,48 @@ const void *class_key(const KernelSet &ks, bool serial)
     return ks.segPB ? ks.segPB : ks.segB;
 }
 
-// Fill kernel for the queue counters (a kernel, not a memset node, so that
-// the captured graph replays it reliably).
-__global__ void k_zero_i32(int *p, int n)
+// Fill kernel for the classes' words {job counter, left to the product path}
+// (a kernel, not a memset node, so that the captured graph replays it reliably).
+__global__ void k_init_words(int *p, int n, int left)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
+    if (i < n) {
+        p[2 * i] = 0;
+        p[2 * i + 1] = left;
+    }
+}
+
+// Segment chains of a batch: the plan of set s (empty: product path only) and
+// the segment length all sets share.  One workgroup (32 segments) per CU, as
+// many as are resident, but segments of at most kBatchChainLen: long ones leave
+// few workgroups of very different cost (K = 8 and K = 64 in one launch), and
+// at this length the warm-up is 8..20 % of the work.  A set takes part where the
+// sets of its K bracket together are long enough (chain_min_T): in a batch the
+// launches are shared.
+constexpr int64_t kBatchChainLen = 512;
+
+void plan_batch_chains(const BatchPlan &bp, std::vector<ChainPlan> *cps)
+{
+    cps->assign(bp.n, ChainPlan());
+    int64_t total = 0, bracket[4] = {};
+    auto bracket_of = [](int K) { return K <= 4 ? 0 : (K <= 16 ? 1 : (K <= 25 ? 2 : 3)); };
+    for (int s = 0; s < bp.n; ++s) {
+        total += bp.T[s];
+        bracket[bracket_of(bp.K[s])] += bp.T[s];
+    }
+    const int64_t segs = 256 * ChainShape{2, 1}.segs();
+    const int64_t L = std::max(kChainMinLen, std::min(kBatchChainLen, (total + segs - 1) / segs));
+    for (int s = 0; s < bp.n; ++s)
+        if (bracket[bracket_of(bp.K[s])] >= chain_min_T(bp.K[s]))
+            (*cps)[s] = cut_chain(bp.T[s], L, ChainShape{2, 1});
+}
+
+// Cost of one chain step of 32 segments, in units of a matrix instruction:
+// the longer of the walker's products and the stager's evaluations.
+double chain_step_cost(int K)
+{
+    const int nsl = (K + 3) / 4, mt = (K + 15) / 16;
+    return std::max(8.0 + mt * nsl, 8.0 + 2.9 * nsl);
 }
 
 const void *serial_kernel(int KP)
@@ -294,6 +336,23 @@ int build(hmm_ctx *ctx, BatchPlan &bp)
     // the most expensive classes first (they start first on the branches)
     std::stable_sort(bp.classes.begin(), bp.classes.end(),
                      [](const BatchClass &x, const BatchClass &y) { return x.cost > y.cost; });
+    // segment chains: plans and workgroups, the most expensive first
+    std::vector<ChainPlan> cps(n);
+    if (bp.chain) plan_batch_chains(bp, &cps);
+    std::vector<ChainJob> cjobs;
+    std::vector<double> ccost(n, 0.0);
+    bp.chain_lds = 0;
+    for (int s = 0; s < n; ++s) {
+        for (int64_t w = 0; w < cps[s].wgs; ++w) cjobs.push_back(ChainJob{w, s, 0});
+        if (cps[s].wgs > 0) {
+            ccost[s] = chain_step_cost(bp.K[s]) * (double)(cps[s].q + 64);
+            bp.chain_lds = std::max(bp.chain_lds, ChainShape{2, 1}.lds(bp.K[s]));
+        }
+    }
+    std::stable_sort(cjobs.begin(), cjobs.end(),
+                     [&](const ChainJob &x, const ChainJob &y) { return ccost[x.set] > ccost[y.set]; });
+    bp.ncjobs = cjobs.size();
+    if (!grid_fits((int64_t)bp.ncjobs, ChainShape{2, 1}.threads())) return HMM_E_UNSUPPORTED;
     // device memory: tables, per-set slots, per-class products
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -307,7 +366,17 @@ int build(hmm_ctx *ctx, BatchPlan &bp)
     const size_t o_pjobs = take(sizeof(FoldJob) * std::max<size_t>(pjobs.size(), 1));
     const size_t o_status = take(sizeof(int) * n);
     const size_t o_ids = take(sizeof(int) * n);
-    const size_t o_queues = take(sizeof(int) * std::max<size_t>(bp.classes.size(), 1));
+    const size_t o_queues = take(2 * sizeof(int) * std::max<size_t>(bp.classes.size(), 1));
+    const size_t o_cjobs = take(sizeof(ChainJob) * std::max<size_t>(cjobs.size(), 1));
+    const size_t o_cls = take(sizeof(int) * n);
+    std::vector<size_t> o_chain(n), o_vs(n), o_ve(n), o_part(n);
+    for (int s = 0; s < n; ++s) {
+        if (cps[s].nb == 0) continue;
+        o_chain[s] = take(sizeof(int) * kChainWords);
+        o_vs[s] = take(sizeof(float) * kp[s] * cps[s].waves);
+        o_ve[s] = take(sizeof(float) * kp[s] * cps[s].waves);
+        o_part[s] = take(sizeof(double) * cps[s].waves);
+    }
     std::vector<size_t> o_sc(n), o_gf(n);
     for (int s = 0; s < n; ++s) {
         const int KP = kp[s];
@@ -336,6 +405,8 @@ int build(hmm_ctx *ctx, BatchPlan &bp)
     bp.pjobs = reinterpret_cast<FoldJob *>(base + o_pjobs);
     int *status = reinterpret_cast<int *>(base + o_status);
     bp.queues = reinterpret_cast<int *>(base + o_queues);
+    bp.cjobs = reinterpret_cast<ChainJob *>(base + o_cjobs);
+    bp.cls = reinterpret_cast<int *>(base + o_cls);
     int n_cu = 0;
     if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess ||
         n_cu < 1) {
@@ -345,7 +416,7 @@ int build(hmm_ctx *ctx, BatchPlan &bp)
     std::vector<int> ids;
     for (size_t ci = 0; ci < bp.classes.size(); ++ci) {
         BatchClass &c = bp.classes[ci];
-        c.queue = bp.queues + ci;
+        c.queue = bp.queues + 2 * ci;
         if (c.serial) {
             c.ids = reinterpret_cast<int *>(base + o_ids) + ids.size();
             ids.insert(ids.end(), c.sets.begin(), c.sets.end());
@@ -357,11 +428,13 @@ int build(hmm_ctx *ctx, BatchPlan &bp)
     }
     std::vector<SetDesc> hs(n);
     std::vector<PrepJob> hp(n);
+    std::vector<int> hc(n);
     for (int s = 0; s < n; ++s) {
         const BatchClass *c = nullptr;
         const void *key = class_key(kss[s], serial);
         for (const auto &cc : bp.classes)
             if (cc.seg == key) c = &cc;
+        hc[s] = (int)(c - bp.classes.data());
         SetDesc &d = hs[s];
         d.obs = Obs{bp.flag + bp.obs_off[s], bp.xy + 2 * bp.obs_off[s], nullptr, kEmisTremor, 0};
         d.sc = reinterpret_cast<const StateConst *>(base + o_sc[s]);
@@ -379,11 +452,23 @@ int build(hmm_ctx *ctx, BatchPlan &bp)
         pj.GF = reinterpret_cast<float *>(base + o_gf[s]);
         pj.status = status + s;
         pj.chain = nullptr;
+        if (cps[s].nb > 0) {
+            Layout ly;
+            ly.chain = o_chain[s];
+            ly.vs = o_vs[s];
+            ly.ve = o_ve[s];
+            ly.part = o_part[s];
+            set_chain(&d, base, ly, cps[s]);
+            pj.chain = d.fail;
+        }
         pj.K = bp.K[s];
         pj.KP = kp[s];
     }
     if (hipMemcpy(bp.sets, hs.data(), sizeof(SetDesc) * n, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(bp.prep, hp.data(), sizeof(PrepJob) * n, hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(bp.cls, hc.data(), sizeof(int) * n, hipMemcpyHostToDevice) != hipSuccess ||
+        (!cjobs.empty() &&
+         hipMemcpy(bp.cjobs, cjobs.data(), sizeof(ChainJob) * cjobs.size(), hipMemcpyHostToDevice) != hipSuccess) ||
         (!jobs.empty() &&
          hipMemcpy(bp.jobs, jobs.data(), sizeof(WgJob) * jobs.size(), hipMemcpyHostToDevice) != hipSuccess) ||
         (!fjobs.empty() &&
@@ -394,6 +479,7 @@ int build(hmm_ctx *ctx, BatchPlan &bp)
          hipMemcpy(reinterpret_cast<int *>(base + o_ids), ids.data(), sizeof(int) * ids.size(),
                    hipMemcpyHostToDevice) != hipSuccess))
         return HMM_E_DEVICE;
+    if (bp.ncjobs > 0 && allow_lds(chain_kernel_batch(), bp.chain_lds) != HMM_OK) return HMM_E_DEVICE;
     for (auto &c : bp.classes) {
         if (c.serial) continue;
         const size_t rb = (size_t)region_bytes(c.ks.KP());
@@ -445,10 +531,21 @@ int enqueue_class(const BatchPlan &bp, const BatchClass &c, hipStream_t st)
 int enqueue(const BatchPlan &bp, hipStream_t st, const BatchClass *only = nullptr, bool branches = false)
 {
     if (!only) hipLaunchKernelGGL(k_prepare_batch, dim3(bp.n), dim3(256), 0, st, bp.prep);
-    // job counters of the persistent launches start at zero on every run
-    if (bp.persistent && !bp.classes.empty() && bp.queues)
-        hipLaunchKernelGGL(k_zero_i32, dim3((unsigned)((bp.classes.size() + 255) / 256)), dim3(256), 0, st,
-                           bp.queues, (int)bp.classes.size());
+    // job counters of the persistent launches start at zero on every run; the
+    // classes' second words at zero with segment chains (raised after them),
+    // at one without
+    if (!bp.classes.empty() && bp.queues)
+        hipLaunchKernelGGL(k_init_words, dim3((unsigned)((bp.classes.size() + 255) / 256)), dim3(256), 0, st,
+                           bp.queues, (int)bp.classes.size(), bp.ncjobs > 0 && !only ? 0 : 1);
+    if (bp.ncjobs > 0 && !only) {
+        for (int mode = 0; mode < 2; ++mode) {
+            void *args[] = {(void *)&bp.sets, (void *)&bp.cjobs, &mode};
+            if (hipLaunchKernel(chain_kernel_batch(), dim3((unsigned)bp.ncjobs), dim3(ChainShape{2, 1}.threads()), args,
+                                bp.chain_lds, st) != hipSuccess)
+                return HMM_E_DEVICE;
+        }
+        if (launch_chain_finish(bp.n, st, bp.sets, bp.cls, bp.queues) != hipSuccess) return HMM_E_DEVICE;
+    }
     if (!branches) {
         for (const auto &c : bp.classes) {
             if (only && &c != only) continue;
@@ -507,7 +604,7 @@ bool same_plan(const BatchPlan &bp, const hmm_ctx *ctx, int n, const int32_t *K,
     if (bp.n != n || bp.algo != algo || bp.params != params || bp.flag != flag || bp.xy != xy || bp.out != out)
         return false;
     if (bp.tuned != ctx->tuned_L || bp.tunedW != ctx->tuned_W || bp.persistent != ctx->batch_persistent ||
-        bp.packing != ctx->packing)
+        bp.packing != ctx->packing || bp.chain != (algo == HMM_BLOCKED_F32 && ctx->default_plan()))
         return false;
     return std::equal(K, K + n, bp.K.begin()) && std::equal(T, T + n, bp.T.begin()) &&
            std::equal(param_off, param_off + n, bp.param_off.begin()) &&
@@ -542,6 +639,7 @@ int get_plan(hmm_ctx *ctx, int n, const int32_t *K, const int64_t *T, const int6
     bp->tunedW = ctx->tuned_W;
     bp->persistent = ctx->batch_persistent;
     bp->packing = ctx->packing;
+    bp->chain = algo == HMM_BLOCKED_F32 && ctx->default_plan();
     int rc = build(ctx, *bp);
     if (rc == HMM_OK && ctx->batch_graph) rc = capture(*bp);
     if (rc != HMM_OK) {
@@ -672,6 +770,7 @@ int hmm_autotune_batched(hmm_ctx *ctx, int32_t n, const int32_t *K, const int64_
     (void)hipEventCreate(&e1);
     const bool graph_was = ctx->batch_graph;
     ctx->batch_graph = false;
+    ctx->no_chain = true;   // the candidates are the product path's
     for (int k : ks) {
         ctx->tuned_L.erase({k, algo});
         ctx->tuned_W.erase({k, algo});
@@ -728,6 +827,7 @@ int hmm_autotune_batched(hmm_ctx *ctx, int32_t n, const int32_t *K, const int64_
             for (int s = 0; s < n; ++s) chosen_L[s] = ctx->tuned_L[{K[s], algo}];
     }
     ctx->batch_graph = graph_was;
+    ctx->no_chain = false;
     (void)hipStreamSynchronize(st);
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);

@@ -223,15 +223,11 @@ struct ChainPlan {
     bool big = false;
 };
 
-// total: observations of all sets that share the launch (T for a single set).
-inline ChainPlan make_chain_plan(int K, int64_t T, int64_t total)
+// T observations in balanced segments of at most L.
+inline ChainPlan cut_chain(int64_t T, int64_t L, ChainShape sh)
 {
     ChainPlan c;
-    if (T < 64) return c;
-    c.big = total >= chain_big_T(K);
-    const ChainShape sh = chain_shape(K, c.big);
-    const int64_t segs = 256 * sh.segs();
-    const int64_t L = std::min(kChainMaxLen, std::max<int64_t>(kChainMinLen, (total + segs - 1) / segs));
+    if (T < 64) return c;   // k_chain reads windows of observations
     c.nb = (T + L - 1) / L;
     c.q = T / c.nb;
     c.r = T % c.nb;
@@ -240,10 +236,23 @@ inline ChainPlan make_chain_plan(int K, int64_t T, int64_t total)
     return c;
 }
 
+inline ChainPlan make_chain_plan(int K, int64_t T)
+{
+    const bool big = T >= chain_big_T(K);
+    const ChainShape sh = chain_shape(K, big);
+    const int64_t segs = 256 * sh.segs();
+    ChainPlan c = cut_chain(T, std::min(kChainMaxLen, std::max(kChainMinLen, (T + segs - 1) / segs)), sh);
+    c.big = big;
+    return c;
+}
+
 // k_chain by live contraction slots and workgroup shape (hmm_chain.hip,
 // hmm_chain_kinds.hip).
 const void *chain_kernel_tremor(int nsl, bool big);
 const void *chain_kernel_kinds(int nsl, bool big);
+// k_chain_batch and k_chain_finish (hmm_chain_batch.hip).
+const void *chain_kernel_batch();
+hipError_t launch_chain_finish(int n, hipStream_t st, const SetDesc *sets, const int *cls, int *words);
 
 inline const void *chain_kernel(int K, bool gen, bool big)
 {
@@ -476,14 +485,13 @@ inline void set_chain(SetDesc *d, void *ws, const Layout &ly, const ChainPlan &c
     d->cr = cp.r;
 }
 
-// The two launches of the segment chains: the chains, then the check across
-// walkers (nothing to check with one walker).
-inline hipError_t launch_chain(const void *fn, unsigned grid, int threads, size_t lds, hipStream_t st, SetDesc one,
-                               const SetDesc *sets, const ChainJob *jobs, bool check)
+// The two launches of a set's segment chains: the chains, then the check
+// across walkers (nothing to check with one walker).
+inline hipError_t launch_chain(const void *fn, const ChainPlan &cp, ChainShape shape, hipStream_t st, SetDesc d)
 {
-    for (int mode = 0; mode < (check ? 2 : 1); ++mode) {
-        void *args[] = {&one, &sets, &jobs, &mode};
-        const hipError_t e = hipLaunchKernel(fn, dim3(grid), dim3(threads), args, lds, st);
+    for (int mode = 0; mode < (cp.waves > 1 ? 2 : 1); ++mode) {
+        void *args[] = {&d, &mode};
+        const hipError_t e = hipLaunchKernel(fn, dim3((unsigned)cp.wgs), dim3(shape.threads()), args, shape.lds(d.K), st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -525,9 +533,7 @@ inline int run_single(hmm_ctx *ctx, void *ws, const KernelSet &ks, SetDesc d, co
         set_chain(&d, ws, ly, cp);
     }
     if (ev0) (void)hipEventRecord(ev0, st);
-    if (chain && launch_chain(chain, (unsigned)cp.wgs, shape.threads(), shape.lds(d.K), st, d, nullptr, nullptr,
-                              cp.waves > 1) != hipSuccess)
-        return HMM_E_DEVICE;
+    if (chain && launch_chain(chain, cp, shape, st, d) != hipSuccess) return HMM_E_DEVICE;
     if (pl.nb > 0) {
         if (launch_seg(seg, (unsigned)pl.n1, pl.waves, seg_lds, st, d, nullptr, nullptr, pl.nb,
                        at<float>(ws, ly.m0), at<long long>(ws, ly.e0), at<long long>(ws, ly.s0)) != hipSuccess)

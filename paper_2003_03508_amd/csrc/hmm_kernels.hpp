@@ -891,9 +891,12 @@ __device__ __forceinline__ void blocked_job(const SetDesc &d, const WgJob &job, 
 // indices from the atomic counter *queue (zeroed before the launch) until
 // they run past the n_jobs entries.  The table is ordered by decreasing cost,
 // so the longest jobs start first and the short ones fill the tail.
+// queue[1] is 0 where the segment chains have served every set of the launch:
+// nothing to do then.
 template <typename Job>
 __device__ __forceinline__ void run_jobs(const WgJob *__restrict__ jobs, int64_t n_jobs, int *queue, Job &&job)
 {
+    if (queue && queue[1] == 0) return;
     __shared__ int next;
     // index of the next job: blockIdx.x without a queue, else from the counter
     auto fetch = [&]() -> int64_t {
@@ -1616,8 +1619,8 @@ __global__ __launch_bounds__(64 * group_waves(S * MT)) void k_fold(SetDesc one, 
         job.set = 0;
     }
     const int K = d.K;
-    if (d.chained()) {
-        if (job.final_) chain_finish(d, smem);
+    if (d.chained()) {   // (a batch finishes such sets in k_chain_finish)
+        if (!BATCH && job.final_) chain_finish(d, smem);
         return;
     }
 
