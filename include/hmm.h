@@ -213,10 +213,14 @@ int hmm_loglik_kind(hmm_ctx *ctx, int32_t kind, int32_t K, const double *delta,
  * out[n] receives ln L of every set, with hmm_loglik's conventions (NaN for
  * invalid parameters or data of that set, -inf for L = 0).
  * algo: HMM_BLOCKED_F32 / _BF16 / _F16.  The context builds a plan (job
- * tables, per-set scratch) for these descriptors and device pointers and, by
- * default, captures the launch sequence in a HIP graph; a later call with
- * identical descriptors and pointers (the parameter VALUES may change)
- * replays the graph.  The plan depends on the segment lengths tuned by
+ * tables, per-set scratch) for these descriptors.  The first call with them
+ * launches it directly; by default the second one captures the launch sequence
+ * in a HIP graph, which later calls replay.  Other device pointers with the
+ * same descriptors cost one small copy of the tables on `stream`.  On a stream
+ * that is being captured a call is recorded launch by launch; it needs a plan
+ * made by an earlier call with the same descriptors and pointers (otherwise
+ * HMM_E_DEVICE), and what it recorded is valid until the context is used with
+ * others.  The plan depends on the segment lengths tuned by
  * hmm_autotune_batched. */
 int hmm_loglik_batched(hmm_ctx *ctx, int32_t n, const int32_t *K, const int64_t *T,
                        const int64_t *param_off, const double *params, int64_t params_len,

@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cstring>
+#include <new>
 #include <numeric>
 
 #include "hmm_host.hpp"
@@ -51,8 +52,15 @@ struct BatchPlan {
     bool persistent = true;
     int packing = 1;
     bool chain = false;      // segment chains first (default tuning knobs, FP32)
-    // device memory
+    // device memory and the pinned host copy of the descriptor tables at its
+    // start (sets and prep jobs first): they grow and are kept from plan to
+    // plan.  `copied` follows the last copy out of the pinned buffer.
     void *mem = nullptr;
+    size_t mem_bytes = 0;
+    char *host = nullptr;
+    size_t host_bytes = 0;
+    size_t o_prep = 0, pointer_bytes = 0, table_bytes = 0;   // offsets in the tables
+    hipEvent_t copied = nullptr;
     SetDesc *sets = nullptr;
     PrepJob *prep = nullptr;
     WgJob *jobs = nullptr;
@@ -65,7 +73,11 @@ struct BatchPlan {
     size_t ncjobs = 0, chain_lds = 0;
     int *cls = nullptr;          // class of every set
     std::vector<BatchClass> classes;
-    // captured launch sequence (classes forked onto parallel branches)
+    // captured launch sequence (classes forked onto parallel branches): from
+    // the second call with the same descriptors on, the first one launches it
+    // directly (a capture costs more than the launches it saves once).
+    // Streams and events are kept from plan to plan.
+    bool launched = false;
     static constexpr int kBranches = 4;
     hipStream_t cap = nullptr;
     hipStream_t aux[kBranches] = {};
@@ -85,7 +97,9 @@ void batch_plan_free(BatchPlan *bp)
         if (bp->join[i]) (void)hipEventDestroy(bp->join[i]);
     }
     if (bp->fork) (void)hipEventDestroy(bp->fork);
+    if (bp->copied) (void)hipEventDestroy(bp->copied);
     if (bp->mem) (void)hipFree(bp->mem);
+    if (bp->host) (void)hipHostFree(bp->host);
     delete bp;
 }
 
@@ -115,6 +129,7 @@ int64_t class_L(const hmm_ctx *ctx, const BatchPlan &bp, const BatchClass &c, in
     int64_t best = kMinL;
     double best_cost = -1.0;
     for (int64_t L = kMinL; L <= 4096; ++L) {
+        if (best_cost >= 0.0 && (double)(L + kWgOverhead) >= best_cost) break;   // rounds >= 1: no better from here on
         int64_t wgs = 0;
         for (int s : c.sets) {
             const int64_t nseg = (bp.T[s] + L - 1) / L;
@@ -210,7 +225,91 @@ const void *serial_kernel(int KP)
     }
 }
 
-int build(hmm_ctx *ctx, BatchPlan &bp)
+// Device memory and pinned table buffer of at least `bytes` (the tables are a
+// part of it).  Work that still reads an old buffer is waited for.
+int ensure_memory(BatchPlan &bp, size_t bytes)
+{
+    if (!bp.copied && hipEventCreateWithFlags(&bp.copied, hipEventDisableTiming) != hipSuccess) return HMM_E_DEVICE;
+    if (bytes > bp.mem_bytes) {
+        if (hipDeviceSynchronize() != hipSuccess) return HMM_E_DEVICE;
+        if (bp.mem) (void)hipFree(bp.mem);
+        bp.mem = nullptr;
+        bp.mem_bytes = 0;
+        if (hipMalloc(&bp.mem, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            bp.mem = nullptr;
+            return HMM_E_NOMEM;
+        }
+        bp.mem_bytes = bytes;
+    }
+    // the last copy out of the pinned buffer is over before it is rewritten
+    if (hipEventSynchronize(bp.copied) != hipSuccess) return HMM_E_DEVICE;
+    if (bp.table_bytes > bp.host_bytes) {
+        if (bp.host) (void)hipHostFree(bp.host);
+        bp.host = nullptr;
+        bp.host_bytes = 0;
+        const size_t want = bp.table_bytes + bp.table_bytes / 4;
+        if (hipHostMalloc(reinterpret_cast<void **>(&bp.host), want, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            bp.host = nullptr;
+            return HMM_E_NOMEM;
+        }
+        bp.host_bytes = want;
+    }
+    return HMM_OK;
+}
+
+// Copies the first `bytes` of the tables, ordered on st after the launches
+// that still read the old ones.
+int upload(BatchPlan &bp, size_t bytes, hipStream_t st)
+{
+    if (hipMemcpyAsync(bp.mem, bp.host, bytes, hipMemcpyHostToDevice, st) != hipSuccess ||
+        hipEventRecord(bp.copied, st) != hipSuccess) {
+        (void)hipGetLastError();
+        return HMM_E_DEVICE;
+    }
+    return HMM_OK;
+}
+
+// New input and output buffers for a plan's descriptors: only the pointers in
+// the tables change.
+int set_pointers(BatchPlan &bp, const double *params, const uint8_t *flag, const double *xy, double *out,
+                 hipStream_t st)
+{
+    if (hipEventSynchronize(bp.copied) != hipSuccess) return HMM_E_DEVICE;
+    SetDesc *hs = reinterpret_cast<SetDesc *>(bp.host);
+    PrepJob *hp = reinterpret_cast<PrepJob *>(bp.host + bp.o_prep);
+    bp.params = params;
+    bp.flag = flag;
+    bp.xy = xy;
+    bp.out = out;
+    for (int s = 0; s < bp.n; ++s) {
+        hs[s].obs = Obs{flag + bp.obs_off[s], xy + 2 * bp.obs_off[s], nullptr, kEmisTremor, 0};
+        hs[s].delta = hp[s].params = params + bp.param_off[s];
+        hs[s].out = out + s;
+    }
+    return upload(bp, bp.pointer_bytes, st);
+}
+
+// Workgroups of a kernel that a CU holds at once (asked once per launch shape).
+int resident_groups(const void *fn, int threads, size_t lds)
+{
+    static std::mutex mu;
+    static std::map<std::pair<const void *, std::pair<int, size_t>>, int> known;
+    std::lock_guard<std::mutex> lock(mu);
+    const auto key = std::make_pair(fn, std::make_pair(threads, lds));
+    auto it = known.find(key);
+    if (it != known.end()) return it->second;
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds) != hipSuccess || per_cu < 1) {
+        (void)hipGetLastError();
+        return 1;
+    }
+    known[key] = per_cu;
+    return per_cu;
+}
+
+int build(hmm_ctx *ctx, BatchPlan &bp, hipStream_t st)
 {
     const int n = bp.n;
     const bool serial = (bp.algo == HMM_SERIAL_F32);
@@ -360,15 +459,20 @@ int build(hmm_ctx *ctx, BatchPlan &bp)
         off = align_up(off + bytes);
         return o;
     };
+    // the tables, copied from the host in one piece
     const size_t o_sets = take(sizeof(SetDesc) * n), o_prep = take(sizeof(PrepJob) * n);
+    bp.o_prep = o_prep;
+    bp.pointer_bytes = off;
     const size_t o_jobs = take(sizeof(WgJob) * std::max<size_t>(jobs.size(), 1));
     const size_t o_fjobs = take(sizeof(FoldJob) * std::max<size_t>(fjobs.size(), 1));
     const size_t o_pjobs = take(sizeof(FoldJob) * std::max<size_t>(pjobs.size(), 1));
-    const size_t o_status = take(sizeof(int) * n);
-    const size_t o_ids = take(sizeof(int) * n);
-    const size_t o_queues = take(2 * sizeof(int) * std::max<size_t>(bp.classes.size(), 1));
     const size_t o_cjobs = take(sizeof(ChainJob) * std::max<size_t>(cjobs.size(), 1));
+    const size_t o_ids = take(sizeof(int) * n);
     const size_t o_cls = take(sizeof(int) * n);
+    bp.table_bytes = off;
+    // what the kernels write
+    const size_t o_status = take(sizeof(int) * n);
+    const size_t o_queues = take(2 * sizeof(int) * std::max<size_t>(bp.classes.size(), 1));
     std::vector<size_t> o_chain(n), o_vs(n), o_ve(n), o_part(n);
     for (int s = 0; s < n; ++s) {
         if (cps[s].nb == 0) continue;
@@ -392,11 +496,8 @@ int build(hmm_ctx *ctx, BatchPlan &bp)
         o_e[ci] = take(sizeof(long long) * KP * np);
         o_s[ci] = take(sizeof(long long) * np);
     }
-    if (hipMalloc(&bp.mem, off) != hipSuccess) {
-        (void)hipGetLastError();
-        bp.mem = nullptr;
-        return HMM_E_NOMEM;
-    }
+    int rc = ensure_memory(bp, off);
+    if (rc != HMM_OK) return rc;
     char *base = static_cast<char *>(bp.mem);
     bp.sets = reinterpret_cast<SetDesc *>(base + o_sets);
     bp.prep = reinterpret_cast<PrepJob *>(base + o_prep);
@@ -464,21 +565,19 @@ int build(hmm_ctx *ctx, BatchPlan &bp)
         pj.K = bp.K[s];
         pj.KP = kp[s];
     }
-    if (hipMemcpy(bp.sets, hs.data(), sizeof(SetDesc) * n, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(bp.prep, hp.data(), sizeof(PrepJob) * n, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(bp.cls, hc.data(), sizeof(int) * n, hipMemcpyHostToDevice) != hipSuccess ||
-        (!cjobs.empty() &&
-         hipMemcpy(bp.cjobs, cjobs.data(), sizeof(ChainJob) * cjobs.size(), hipMemcpyHostToDevice) != hipSuccess) ||
-        (!jobs.empty() &&
-         hipMemcpy(bp.jobs, jobs.data(), sizeof(WgJob) * jobs.size(), hipMemcpyHostToDevice) != hipSuccess) ||
-        (!fjobs.empty() &&
-         hipMemcpy(bp.fjobs, fjobs.data(), sizeof(FoldJob) * fjobs.size(), hipMemcpyHostToDevice) != hipSuccess) ||
-        (!pjobs.empty() &&
-         hipMemcpy(bp.pjobs, pjobs.data(), sizeof(FoldJob) * pjobs.size(), hipMemcpyHostToDevice) != hipSuccess) ||
-        (!ids.empty() &&
-         hipMemcpy(reinterpret_cast<int *>(base + o_ids), ids.data(), sizeof(int) * ids.size(),
-                   hipMemcpyHostToDevice) != hipSuccess))
-        return HMM_E_DEVICE;
+    auto put = [&](size_t o, const void *src, size_t bytes) {
+        if (bytes > 0) std::memcpy(bp.host + o, src, bytes);
+    };
+    put(o_sets, hs.data(), sizeof(SetDesc) * n);
+    put(o_prep, hp.data(), sizeof(PrepJob) * n);
+    put(o_jobs, jobs.data(), sizeof(WgJob) * jobs.size());
+    put(o_fjobs, fjobs.data(), sizeof(FoldJob) * fjobs.size());
+    put(o_pjobs, pjobs.data(), sizeof(FoldJob) * pjobs.size());
+    put(o_cjobs, cjobs.data(), sizeof(ChainJob) * cjobs.size());
+    put(o_ids, ids.data(), sizeof(int) * ids.size());
+    put(o_cls, hc.data(), sizeof(int) * n);
+    rc = upload(bp, bp.table_bytes, st);
+    if (rc != HMM_OK) return rc;
     if (bp.ncjobs > 0 && allow_lds(chain_kernel_batch(), bp.chain_lds) != HMM_OK) return HMM_E_DEVICE;
     for (auto &c : bp.classes) {
         if (c.serial) continue;
@@ -488,12 +587,7 @@ int build(hmm_ctx *ctx, BatchPlan &bp)
         // persistent launch: as many workgroups as are resident at once
         c.grid = 0;
         if (bp.persistent) {
-            int per_cu = 0;
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, c.seg, 64 * c.waves, c.seg_lds) != hipSuccess ||
-                per_cu < 1) {
-                (void)hipGetLastError();
-                per_cu = 1;
-            }
+            const int per_cu = resident_groups(c.seg, 64 * c.waves, c.seg_lds);
             c.grid = (int)std::min<int64_t>((int64_t)c.njobs, (int64_t)per_cu * n_cu);
         }
     }
@@ -571,14 +665,22 @@ int enqueue(const BatchPlan &bp, hipStream_t st, const BatchClass *only = nullpt
     return HMM_OK;
 }
 
-int capture(BatchPlan &bp)
+// Streams and events of the branches (and the capture stream), once per context.
+int ensure_branches(BatchPlan &bp)
 {
+    if (bp.fork) return HMM_OK;
     if (hipStreamCreateWithFlags(&bp.cap, hipStreamNonBlocking) != hipSuccess) return HMM_E_DEVICE;
     for (int b = 0; b < BatchPlan::kBranches; ++b) {
         if (hipStreamCreateWithFlags(&bp.aux[b], hipStreamNonBlocking) != hipSuccess) return HMM_E_DEVICE;
         if (hipEventCreateWithFlags(&bp.join[b], hipEventDisableTiming) != hipSuccess) return HMM_E_DEVICE;
     }
     if (hipEventCreateWithFlags(&bp.fork, hipEventDisableTiming) != hipSuccess) return HMM_E_DEVICE;
+    return HMM_OK;
+}
+
+int capture(BatchPlan &bp)
+{
+    if (ensure_branches(bp) != HMM_OK) return HMM_E_DEVICE;
     if (hipStreamBeginCapture(bp.cap, hipStreamCaptureModeThreadLocal) != hipSuccess) return HMM_E_DEVICE;
     int rc = enqueue(bp, bp.cap, nullptr, bp.classes.size() > 1);
     hipGraph_t g = nullptr;
@@ -597,12 +699,11 @@ int capture(BatchPlan &bp)
     return HMM_OK;
 }
 
+// The plan was built for these descriptors and options (any buffers).
 bool same_plan(const BatchPlan &bp, const hmm_ctx *ctx, int n, const int32_t *K, const int64_t *T,
-               const int64_t *param_off, const double *params, const int64_t *obs_off, const uint8_t *flag,
-               const double *xy, int algo, double *out)
+               const int64_t *param_off, const int64_t *obs_off, int algo)
 {
-    if (bp.n != n || bp.algo != algo || bp.params != params || bp.flag != flag || bp.xy != xy || bp.out != out)
-        return false;
+    if (bp.n != n || bp.algo != algo) return false;
     if (bp.tuned != ctx->tuned_L || bp.tunedW != ctx->tuned_W || bp.persistent != ctx->batch_persistent ||
         bp.packing != ctx->packing || bp.chain != (algo == HMM_BLOCKED_F32 && ctx->default_plan()))
         return false;
@@ -611,20 +712,53 @@ bool same_plan(const BatchPlan &bp, const hmm_ctx *ctx, int n, const int32_t *K,
            std::equal(obs_off, obs_off + n, bp.obs_off.begin());
 }
 
+bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &c) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return c != hipStreamCaptureStatusNone;
+}
+
+// The context's plan for these descriptors and buffers, its tables in place for
+// what is enqueued on st next.  A stream that is being captured can use a plan
+// that is there, but not change one.
 int get_plan(hmm_ctx *ctx, int n, const int32_t *K, const int64_t *T, const int64_t *param_off,
              const double *params, const int64_t *obs_off, const uint8_t *flag, const double *xy, int algo,
-             double *out, BatchPlan **res)
+             double *out, hipStream_t st, BatchPlan **res)
 {
-    if (ctx->batch && same_plan(*ctx->batch, ctx, n, K, T, param_off, params, obs_off, flag, xy, algo, out)) {
-        *res = ctx->batch;
-        return HMM_OK;
+    BatchPlan *old = ctx->batch;
+    if (old && same_plan(*old, ctx, n, K, T, param_off, obs_off, algo)) {
+        *res = old;
+        if (old->params == params && old->flag == flag && old->xy == xy && old->out == out) return HMM_OK;
+        return capturing(st) ? HMM_E_DEVICE : set_pointers(*old, params, flag, xy, out, st);
     }
-    if (ctx->batch) {
-        if (hipDeviceSynchronize() != hipSuccess) return HMM_E_DEVICE;
-        batch_plan_free(ctx->batch);
+    if (capturing(st)) return HMM_E_DEVICE;
+    BatchPlan *bp = new (std::nothrow) BatchPlan;
+    if (!bp) return HMM_E_NOMEM;
+    if (old) {
+        // a graph may still be running; direct launches are ordered before
+        // the new tables by the stream
+        if (old->exec && hipDeviceSynchronize() != hipSuccess) {
+            delete bp;
+            return HMM_E_DEVICE;
+        }
+        std::swap(bp->mem, old->mem);
+        std::swap(bp->mem_bytes, old->mem_bytes);
+        std::swap(bp->host, old->host);
+        std::swap(bp->host_bytes, old->host_bytes);
+        std::swap(bp->copied, old->copied);
+        std::swap(bp->cap, old->cap);
+        std::swap(bp->fork, old->fork);
+        for (int b = 0; b < BatchPlan::kBranches; ++b) {
+            std::swap(bp->aux[b], old->aux[b]);
+            std::swap(bp->join[b], old->join[b]);
+        }
+        batch_plan_free(old);
         ctx->batch = nullptr;
     }
-    BatchPlan *bp = new BatchPlan;
     bp->n = n;
     bp->algo = algo;
     bp->K.assign(K, K + n);
@@ -640,9 +774,9 @@ int get_plan(hmm_ctx *ctx, int n, const int32_t *K, const int64_t *T, const int6
     bp->persistent = ctx->batch_persistent;
     bp->packing = ctx->packing;
     bp->chain = algo == HMM_BLOCKED_F32 && ctx->default_plan();
-    int rc = build(ctx, *bp);
-    if (rc == HMM_OK && ctx->batch_graph) rc = capture(*bp);
+    const int rc = build(ctx, *bp, st);
     if (rc != HMM_OK) {
+        (void)hipDeviceSynchronize();   // an earlier call may still use the buffers
         batch_plan_free(bp);
         return rc;
     }
@@ -690,17 +824,25 @@ int hmm_loglik_batched(hmm_ctx *ctx, int32_t n, const int32_t *K, const int64_t 
     if (!dg.ok) return HMM_E_DEVICE;
     hipStream_t st = static_cast<hipStream_t>(stream);
     BatchPlan *bp = nullptr;
-    rc = get_plan(ctx, n, K, T, param_off, params, obs_off, flag, xy, algo, out, &bp);
+    rc = get_plan(ctx, n, K, T, param_off, params, obs_off, flag, xy, algo, out, st, &bp);
     if (rc != HMM_OK) return rc;
-    if (bp->exec) {
+    const bool user_capture = capturing(st);
+    if (ctx->batch_graph && bp->launched && !bp->exec && !user_capture) {
+        rc = capture(*bp);
+        if (rc != HMM_OK) return rc;
+    }
+    if (bp->exec && !user_capture) {
         if (hipGraphLaunch(bp->exec, st) != hipSuccess) {
             (void)hipGetLastError();
             return HMM_E_DEVICE;
         }
         return HMM_OK;
     }
-    rc = enqueue(*bp, st);
+    const bool branches = bp->classes.size() > 1 && ctx->batch_graph && !user_capture;
+    if (branches && ensure_branches(*bp) != HMM_OK) return HMM_E_DEVICE;
+    rc = enqueue(*bp, st, nullptr, branches);
     if (rc != HMM_OK) return rc;
+    bp->launched = true;
     return hipGetLastError() == hipSuccess ? HMM_OK : HMM_E_DEVICE;
 }
 
@@ -763,6 +905,8 @@ int hmm_autotune_batched(hmm_ctx *ctx, int32_t n, const int32_t *K, const int64_
     std::vector<int> ks(K, K + n);
     std::sort(ks.begin(), ks.end());
     ks.erase(std::unique(ks.begin(), ks.end()), ks.end());
+    // the candidates' plans reuse the context's buffers on a stream of their own
+    if (hipDeviceSynchronize() != hipSuccess) return HMM_E_DEVICE;
     hipStream_t st = nullptr;
     if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) return HMM_E_DEVICE;
     hipEvent_t e0, e1;
@@ -790,7 +934,7 @@ int hmm_autotune_batched(hmm_ctx *ctx, int32_t n, const int32_t *K, const int64_
                 ctx->tuned_W[{k, algo}] = wdiv ? -wdiv : 0;
             }
             BatchPlan *bp = nullptr;
-            rc = get_plan(ctx, n, K, T, param_off, params, obs_off, flag, xy, algo, out, &bp);
+            rc = get_plan(ctx, n, K, T, param_off, params, obs_off, flag, xy, algo, out, st, &bp);
             if (rc != HMM_OK) break;
             hipLaunchKernelGGL(k_prepare_batch, dim3(bp->n), dim3(256), 0, st, bp->prep);
             for (const auto &c : bp->classes) {
