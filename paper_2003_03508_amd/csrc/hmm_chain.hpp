@@ -203,8 +203,8 @@ struct ObsWindow {
 // its 16 segments, E[state][4 * segment + step].
 //   ê = 2^(lam - sh), lam = log2 e in FP64 (the formula of
 //   state_log2_emission / generic_log2_emission), sh = floor(max_k lam):
-// the largest ê of a step lies in [1, 2).  lam - sh = n + f with n the nearest
-// integer, from the low word of lam + (1.5 * 2^52 - sh); only f is rounded to
+// the largest ê of a step lies in [1, 2).  lam - sh = n + f, f in [0, 1), with n
+// from the low word of (lam - f) + (1.5 * 2^52 - sh); only f is rounded to
 // FP32.  0 below 2^-200 and for steps without an observation.
 //
 // Two layouts, by how many state constants a lane can hold:
@@ -264,11 +264,17 @@ __device__ __forceinline__ int chain_shift(float m)
     return (int)floorf(__builtin_amdgcn_fmed3f(m, -5.0e8f, 5.0e8f));
 }
 
+// The fraction is taken in [0, 1), as the product path's emission stage takes
+// it, so both round a step's emissions alike: steps without a location repeat
+// the same K roundings, which move ln L by 1e-9 relative (a fraction in [-1/2,
+// 1/2) rounds finer but differently, and moved it by up to 5e-9 against the
+// product path; now 1e-11..3e-10.  K = 25, T = 105,000: 50.3 -> 54.5 us,
+// T = 1e6: 92.4 -> 93.6 us).
 __device__ __forceinline__ float chain_emission(double lam, double magic, double low)
 {
     const double l = max_f64(lam, low);
-    const double t = l + magic;
-    return __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f((float)(l - (t - magic))), __double2loint(t));
+    const double f = __builtin_amdgcn_fract(l);
+    return __builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f((float)f), __double2loint((l - f) + magic));
 }
 
 // Segment b of a set as a pair sees it: its first observation relative to the
