@@ -600,6 +600,12 @@ int hmm_em_step(hmm_ctx *ctx, int32_t K, const double *delta, const double *Gamm
  * backpointers inside every segment between its two boundary states.  Ties
  * go to the smallest state index.  1 <= K <= 80 (64 < K: two wavefronts per
  * segment, the matrix exchanged through LDS).
+ * With the automatic segment length and T >= 1000, plain score vectors over
+ * segments started 96 observations early and carried on 64 past their end come
+ * first; the call is served by them when every segment's start vector and end
+ * state are verified, on the device, to be its neighbour's (segments that
+ * differ are run again once from their neighbour), and by the products
+ * otherwise or when Gamma has an entry below 2^-56.
  *   path   device int32 [T]: s_0 .. s_{T-1} (required when T > 0)
  *   first  device int32 [1]: s_{-1}
  *   score  device double [1]: the maximum (natural log)

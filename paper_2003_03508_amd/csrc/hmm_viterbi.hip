@@ -17,6 +17,11 @@
 // the bottom every segment runs the plain Viterbi recursion between its two
 // boundary states with backpointers and writes its part of the path.  Ties
 // go to the smallest state index everywhere, as in the textbook recursion.
+//
+// This product path runs where a segment length or the fold width is set, for
+// the shortest records, and where the verified score vectors over segments
+// (hmm_vit_chain.hpp) ahead of it did not serve the call; otherwise its
+// launches return at once (4.5 us each).
 #include <algorithm>
 #include <climits>
 #include <cmath>
@@ -26,6 +31,7 @@
 #include <type_traits>
 
 #include "hmm_host.hpp"
+#include "hmm_vit_host.hpp"
 
 using namespace hmm;
 using namespace hmmh;
@@ -56,9 +62,17 @@ struct VitDesc {
     const double *Gamma;      // [K][K]
     const double *delta;      // [K]
     int *status;              // bit mask: kBadParams (k_prepare), kBadData (k_vit_segment)
+    const int *fail;          // segment chains: 0 where they served the call; null without them
     int64_t T, L, nb;
     int K, pad;
 };
+
+// The segment chains' answer stands: every product kernel returns at once.
+// (With invalid parameters or data the product kernels write the -1 path.)
+__device__ __forceinline__ bool vit_served(const int *fail, const int *status)
+{
+    return fail && *fail == 0 && *status == 0;
+}
 
 // log2 Gamma (KB x KB, -inf outside K) into LDS.
 template <int KB>
@@ -163,7 +177,7 @@ __global__ __launch_bounds__(64 * vit_waves<KB>()) void k_vit_segment(VitDesc d,
     __shared__ __attribute__((aligned(16))) float lam[NW][KB * kVitSegChunk];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t b = (int64_t)blockIdx.x * NW + w;
-    if (b >= d.nb || *d.status != 0) return;
+    if (b >= d.nb || *d.status != 0 || vit_served(d.fail, d.status)) return;
     const int64_t t0 = b * d.L, t1 = min(d.T, t0 + d.L);
     const int j = lane % KB, ib = lane / KB;
     float lgc[KB];
@@ -220,8 +234,9 @@ __global__ __launch_bounds__(64 * vit_waves<KB>()) void k_vit_segment(VitDesc d,
 // largest entry; off[q] = sum of the children's offsets + renormalisation.
 template <int KB>
 __global__ __launch_bounds__(64) void k_vit_fold(int64_t n, const float *Vin, const double *offin, float *Vout,
-                                                 double *offout)
+                                                 double *offout, const int *fail, const int *status)
 {
+    if (vit_served(fail, status)) return;
     constexpr int R = vit_rows<KB>(), RS = 64 / KB;
     __shared__ __attribute__((aligned(16))) float P[KB * KB];
     const int lane = threadIdx.x, j = lane % KB, ib = lane / KB;
@@ -295,8 +310,9 @@ template <int KB>
 __global__ __launch_bounds__(64) void k_vit_decode(int K, int64_t n, const float *V, const double *off,
                                                    const int32_t *pend, const int32_t *pfirst, int32_t *cend,
                                                    int32_t *first, double *score, const double *delta,
-                                                   const int *status)
+                                                   const int *status, const int *fail)
 {
+    if (vit_served(fail, status)) return;
     __shared__ double dv[64];
     __shared__ int32_t psi[kVitG][KB];
     const int lane = threadIdx.x;
@@ -373,6 +389,7 @@ __global__ __launch_bounds__(64 * vit_waves<KB>()) void k_vit_local(VitDesc d, c
     __shared__ __attribute__((aligned(16))) float dv[NW][KB];
     __shared__ __attribute__((aligned(16))) float lam[NW][KB * kChunk];
     extern __shared__ uint8_t psi[];   // NW x (L x KB) backpointers, sized at launch
+    if (vit_served(d.fail, d.status)) return;
     load_lg<KB>(d, lg);
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int64_t b = (int64_t)blockIdx.x * NW + w;
@@ -488,7 +505,7 @@ __global__ __launch_bounds__(vit_rows_threads<KW>()) void k_vit_segment_rows(Vit
     __shared__ float red[vit_rows_threads<KW>() / 64];
     __shared__ int badw;
     const int64_t b = blockIdx.x;
-    if (b >= d.nb || *d.status != 0) return;
+    if (b >= d.nb || *d.status != 0 || vit_served(d.fail, d.status)) return;
     const int K = d.K, t = threadIdx.x, w = t >> 6;
     const bool live = t < NP * KW;
     const int j = live ? t % KW : KW, i0 = live ? (t / KW) * HR : 0;
@@ -554,8 +571,10 @@ __global__ __launch_bounds__(vit_rows_threads<KW>()) void k_vit_segment_rows(Vit
 // with the running product in LDS (two buffers), thread j computing column j;
 // renormalisation folded into the next product as in k_vit_segment_rows.
 __global__ __launch_bounds__(kVitWideThreads) void k_vit_fold_wide(int64_t n, const float *Vin, const double *offin,
-                                                                   float *Vout, double *offout)
+                                                                   float *Vout, double *offout,
+                                                                   const int *fail, const int *status)
 {
+    if (vit_served(fail, status)) return;
     constexpr int KW = kVitWide;
     __shared__ __attribute__((aligned(16))) float P[2][KW * KW];
     __shared__ float red[2];
@@ -613,8 +632,10 @@ __global__ __launch_bounds__(kVitWideThreads) void k_vit_decode_wide(int K, int6
                                                                      const double *off, const int32_t *pend,
                                                                      const int32_t *pfirst, int32_t *cend,
                                                                      int32_t *first, double *score,
-                                                                     const double *delta, const int *status)
+                                                                     const double *delta, const int *status,
+                                                                     const int *fail)
 {
+    if (vit_served(fail, status)) return;
     constexpr int KW = kVitWide;
     __shared__ double dv[kVitWideThreads];
     __shared__ int32_t psi[kVitG][KW];
@@ -689,6 +710,7 @@ __global__ __launch_bounds__(kVitWideThreads) void k_vit_local_wide(VitDesc d, c
     __shared__ __attribute__((aligned(16))) float lam[KW * kChunk];
     __shared__ float red[2];
     extern __shared__ uint8_t psi[];
+    if (vit_served(d.fail, d.status)) return;
     load_lg<KW>(d, lg);
     const int64_t b = blockIdx.x;
     if (b >= d.nb) return;
@@ -738,15 +760,77 @@ __global__ __launch_bounds__(kVitWideThreads) void k_vit_local_wide(VitDesc d, c
     }
 }
 
-// Score in natural log; NaN, s_-1 = -1 for invalid parameters or data.
-__global__ void k_vit_finish(const int *status, double *score, int32_t *first)
+// k_prepare with log2 Gamma in place of Gamma: K^2 logarithms in FP64, once
+// (each segment of the chains taking its own columns' would spend 7 us on it
+// at K = 64).
+__global__ __launch_bounds__(1024) void k_vit_prepare(int K, int KB, const double *__restrict__ delta,
+                                                      const double *__restrict__ Gamma, const double *__restrict__ p,
+                                                      const double *__restrict__ mu, const double *__restrict__ Sigma,
+                                                      StateConst *__restrict__ sc, float *__restrict__ LG,
+                                                      int *__restrict__ status, int *__restrict__ chain)
 {
-    if (threadIdx.x != 0) return;
+    __shared__ int bad;
+    __shared__ unsigned red[2];
+    if (threadIdx.x == 0) {
+        bad = 0;
+        red[0] = 0x7f800000u;
+        red[1] = 0u;
+    }
+    __syncthreads();
+    int mybad = 0;
+    for (int k = threadIdx.x; k < KB; k += blockDim.x) {
+        mybad |= prepare_state(k, K, p, mu, Sigma, sc);
+        if (k < K && !(isfinite(delta[k]) && delta[k] >= 0.0)) mybad = 1;
+    }
+    mybad |= prepare_gamma(K, KB, Gamma, LG, chain != nullptr, red);
+    if (chain)
+        for (int idx = threadIdx.x; idx < KB * KB; idx += blockDim.x) {   // the entries this thread has written
+            const int i = idx / KB, j = idx % KB;
+            LG[idx] = (i < K && j < K) ? (float)log2(Gamma[(int64_t)i * K + j]) : -INFINITY;
+        }
+    if (mybad) atomicOr(&bad, 1);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        *status = bad ? kBadParams : 0;
+        if (chain) write_chain_words(red, chain);
+    }
+}
+
+// Score in natural log; NaN, s_-1 = -1 for invalid parameters or data.  Where
+// the segment chains served the call: their scores added in a fixed order.
+__global__ __launch_bounds__(1024) void k_vit_finish(const int *status, VitChain v, double *score, int32_t *first)
+{
+    __shared__ double red[1024];
     if (*status != 0) {
-        *score = __builtin_nan("");
-        *first = -1;
-    } else {
-        *score = *score * 0.69314718055994530941723212145818;
+        if (threadIdx.x == 0) {
+            *score = __builtin_nan("");
+            *first = -1;
+        }
+        return;
+    }
+    if (!vit_served(v.fail, status)) {
+        if (threadIdx.x == 0) *score = *score * kLn2;
+        return;
+    }
+    double s = 0.0;
+    int64_t i = threadIdx.x;
+    for (; i + 7 * 1024 < v.fnb; i += 8 * 1024) {   // eight loads in flight
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = v.acc[i + u * 1024];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += x[u];
+    }
+    for (; i < v.fnb; i += 1024) s += v.acc[i];
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int o = 512; o > 0; o >>= 1) {
+        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        *score = red[0] * kLn2;
+        *first = v.pre[0];
     }
 }
 
@@ -852,13 +936,52 @@ int viterbi_impl(hmm_ctx *ctx, int32_t K, const double *delta, const double *Gam
         o_o[l] = take(sizeof(double) * n);
         o_e[l] = take(sizeof(int32_t) * n);
     }
+    const size_t o_chain = take(sizeof(int) * kChainWords);
+    VitChainPlan cp;
+    if (ctx->default_plan()) cp = make_vit_chain_plan(K, T, L);
+    const size_t o_sv = take(sizeof(float) * cp.kr * (size_t)cp.nb), o_ev = take(sizeof(float) * cp.kr * (size_t)cp.nb);
+    const size_t o_end = take(sizeof(int32_t) * (size_t)cp.nb), o_pre = take(sizeof(int32_t) * (size_t)cp.nb);
+    const size_t o_acc = take(sizeof(double) * (size_t)(cp.nb > 0 ? nb : 0));
+    const size_t o_mx = take(sizeof(float) * (size_t)(cp.nb > 0 ? T : 0));
     int rc = ensure_ws(ctx, off);
+    if (rc == HMM_E_NOMEM && cp.nb > 0) {   // the chains' vectors come last: without them
+        cp.nb = 0;
+        rc = ensure_ws(ctx, o_sv);
+    }
     if (rc != HMM_OK) return rc;
     void *ws = ctx->ws;
     int *status = at<int>(ws, o_status);
+    int *chain = cp.nb > 0 ? at<int>(ws, o_chain) : nullptr;
     StateConst *sc = at<StateConst>(ws, o_sc);
-    hipLaunchKernelGGL(k_prepare, dim3(1), dim3(256), 0, st, (int)kEmisTremor, K, KB, delta, Gamma, p, mu, Sigma, sc,
-                       at<float>(ws, o_gf), status, (int *)nullptr);
+    hipLaunchKernelGGL(k_vit_prepare, dim3(1), dim3(1024), 0, st, K, KB, delta, Gamma, p, mu, Sigma, sc,
+                       at<float>(ws, o_gf), status, chain);
+    VitChain v{};
+    v.fail = chain;
+    if (cp.nb > 0) {
+        v.flag = flag;
+        v.xy = xy;
+        v.sc = sc;
+        v.lg = at<float>(ws, o_gf);
+        v.delta = delta;
+        v.status = status;
+        v.sv = at<float>(ws, o_sv);
+        v.ev = at<float>(ws, o_ev);
+        v.endst = at<int32_t>(ws, o_end);
+        v.pre = at<int32_t>(ws, o_pre);
+        v.acc = at<double>(ws, o_acc);
+        v.mx = at<float>(ws, o_mx);
+        v.path = path;
+        v.fnb = nb;
+        v.fL = L;
+        v.T = T;
+        v.nb = cp.nb;
+        v.q = T / cp.nb;
+        v.r = T % cp.nb;
+        v.K = K;
+        v.KB = KB;
+        v.rows = cp.rows();
+        if (launch_vit_chain(cp, v, st) != hipSuccess) return HMM_E_DEVICE;
+    }
     VitDesc d;
     d.flag = flag;
     d.xy = xy;
@@ -866,6 +989,7 @@ int viterbi_impl(hmm_ctx *ctx, int32_t K, const double *delta, const double *Gam
     d.Gamma = Gamma;
     d.delta = delta;
     d.status = status;
+    d.fail = chain;
     d.T = T;
     d.L = L;
     d.nb = nb;
@@ -885,11 +1009,11 @@ int viterbi_impl(hmm_ctx *ctx, int32_t K, const double *delta, const double *Gam
             if constexpr (KB == kVitWide)
                 hipLaunchKernelGGL(k_vit_fold_wide, dim3((unsigned)cnt[l]), dim3(kVitWideThreads), 0, st, cnt[l - 1],
                                    at<float>(ws, o_v[l - 1]), at<double>(ws, o_o[l - 1]), at<float>(ws, o_v[l]),
-                                   at<double>(ws, o_o[l]));
+                                   at<double>(ws, o_o[l]), (const int *)chain, (const int *)status);
             else
                 hipLaunchKernelGGL(k_vit_fold<KB>, dim3((unsigned)cnt[l]), dim3(64), 0, st, cnt[l - 1],
                                    at<float>(ws, o_v[l - 1]), at<double>(ws, o_o[l - 1]), at<float>(ws, o_v[l]),
-                                   at<double>(ws, o_o[l]));
+                                   at<double>(ws, o_o[l]), (const int *)chain, (const int *)status);
         }
     }
     // top level, then every level down to the segments
@@ -898,7 +1022,7 @@ int viterbi_impl(hmm_ctx *ctx, int32_t K, const double *delta, const double *Gam
     const unsigned dec_threads = KB == kVitWide ? kVitWideThreads : 64;
     auto decode = [&](unsigned grid, int64_t n, const float *V, const double *offs, const int32_t *pend,
                       const int32_t *pfirst, int32_t *cend) {
-        void *args[] = {&K, &n, &V, &offs, &pend, &pfirst, &cend, &first, &score, (void *)&delta, &status};
+        void *args[] = {&K, &n, &V, &offs, &pend, &pfirst, &cend, &first, &score, (void *)&delta, &status, &chain};
         return hipLaunchKernel(dec, dim3(grid), dim3(dec_threads), args, 0, st) == hipSuccess;
     };
     if (!decode(1, nb > 0 ? cnt[nlev - 1] : 0, at<float>(ws, o_v[nlev - 1]), at<double>(ws, o_o[nlev - 1]), nullptr,
@@ -919,7 +1043,7 @@ int viterbi_impl(hmm_ctx *ctx, int32_t K, const double *delta, const double *Gam
                             st) != hipSuccess)
             return HMM_E_DEVICE;
     }
-    hipLaunchKernelGGL(k_vit_finish, dim3(1), dim3(64), 0, st, status, score, first);
+    hipLaunchKernelGGL(k_vit_finish, dim3(1), dim3(1024), 0, st, (const int *)status, v, score, first);
     return hipGetLastError() == hipSuccess ? HMM_OK : HMM_E_DEVICE;
 }
 
