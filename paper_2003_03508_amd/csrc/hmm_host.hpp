@@ -143,14 +143,7 @@ struct Plan {
     bool packed = false;  // k_blocked_packed: G segments per wavefront
 };
 
-// Shortest automatic segment.  One FP32 tile (K <= 16): a short record does not
-// fill the GPU, and the call waits for one segment's steps and one more fold
-// level at most, so shorter is faster (K = 3, T = 2000: 23.1 us with 32, 20.3
-// with 16, 19.2 with 8; T = 10,000: 28.2, 24.9, 23.5; K = 13, T = 10,000: 47.9,
-// 41.6, 38.1).  The other kernels keep 32.
-inline int min_segment(int32_t algo, int KP) { return algo == HMM_BLOCKED_F32 && KP == 16 ? 8 : 32; }
-
-inline Plan make_plan(const hmm_ctx *ctx, int KP, int64_t T, int packG, int packWaves, int segWaves, int minLen)
+inline Plan make_plan(const hmm_ctx *ctx, int KP, int64_t T, int packG = 0, int packWaves = 0, int segWaves = 0)
 {
     Plan p;
     p.W = segWaves > 0 ? segWaves : group_waves(KP);
@@ -179,14 +172,14 @@ inline Plan make_plan(const hmm_ctx *ctx, int KP, int64_t T, int packG, int pack
         }
         return p;
     }
-    // One workgroup of W segments per CU (256 CUs), segments of at least
-    // minLen observations.
+    // One workgroup of W segments per CU (256 CUs), segments of at least 32
+    // observations.
     if (ctx->block_len > 0) {
         p.L = ctx->block_len;
     } else {
         const int64_t target = 256 * (int64_t)p.W;
         p.L = (T + target - 1) / target;
-        p.L = std::max<int64_t>(p.L, minLen);
+        if (p.L < 32) p.L = 32;
     }
     p.nb = T > 0 ? (T + p.L - 1) / p.L : 0;
     p.n1 = (p.nb + p.W - 1) / p.W;
