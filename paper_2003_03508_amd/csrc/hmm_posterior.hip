@@ -201,7 +201,10 @@ __device__ void msg_forward(int K, const float *M, const long long *E, double (&
 // without bank conflicts):
 //   (M c)_i = 2^(E_i + h_i) sum_j M~_ij cm_j 2^(ce_j - h_i),
 // h_i the largest ce_j over the terms of row i, so each row keeps its own
-// scale.  Lane i < K holds (cm_i, ce_i), mirrored in LDS (sm, se); lanes of
+// scale.  Where the state of the largest ce_j has no zero in its column of M~,
+// h_i is the same for every row and each lane scales its own state once for
+// all (the same bits: a chain of exponent shifts per term and row is what
+// bounds the level otherwise: 36 -> 23 us for 16 products, K = 25).  Lane i < K holds (cm_i, ce_i), mirrored in LDS (sm, se); lanes of
 // padded states hold 0, so their terms drop out of the branch-free loops.
 template <int KP>
 __device__ void msg_backward(int K, const float *Mt, const long long *E, double (&cm)[msg_ns<KP>()],
@@ -209,6 +212,58 @@ __device__ void msg_backward(int K, const float *Mt, const long long *E, double 
 {
     constexpr int NS = msg_ns<KP>();
     const int j = threadIdx.x & 63;
+    {
+        // largest exponent among the live states, and the first state with it
+        long long h = LLONG_MIN;
+#pragma unroll
+        for (int q = 0; q < NS; ++q) h = (cm[q] > 0.0 && ce[q] > h) ? ce[q] : h;
+        h = wmax_i64(h);
+        int at = 0;
+#pragma unroll
+        for (int q = NS - 1; q >= 0; --q) {
+            const unsigned long long has = __ballot(cm[q] > 0.0 && ce[q] == h);
+            at = has ? __ffsll(has) - 1 + 64 * q : at;
+        }
+        bool common = h != LLONG_MIN;
+#pragma unroll
+        for (int q = 0; q < NS; ++q) {
+            const int i = j + 64 * q;
+            common = common && (i >= K || Mt[at * KP + (i < KP ? i : 0)] != 0.f);
+        }
+        if (__all(common)) {
+#pragma clang fp contract(off)
+#pragma unroll
+            for (int q = 0; q < NS; ++q) {
+                long long sh = ce[q] - h;
+                sh = sh < -1100 ? -1100 : (sh > 0 ? 0 : sh);
+                sm[j + 64 * q] = cm[q] > 0.0 ? ldexp(cm[q], (int)sh) : 0.0;
+            }
+            wsync();
+            double mnew[NS];
+            long long enew[NS];
+#pragma unroll
+            for (int q = 0; q < NS; ++q) {
+                const int i = j + 64 * q, ic = i < KP ? i : 0;
+                double sum = 0.0;
+#pragma unroll
+                for (int u = 0; u < KP; ++u) sum += (double)Mt[u * KP + ic] * sm[u];
+                int ex = 0;
+                const double m = frexp(sum, &ex);
+                mnew[q] = i < K ? m : 0.0;
+                enew[q] = i < K && m > 0.0 ? E[ic] + h + ex : 0;
+            }
+            wsync();
+#pragma unroll
+            for (int q = 0; q < NS; ++q) {
+                cm[q] = mnew[q];
+                ce[q] = enew[q];
+                sm[j + 64 * q] = cm[q];
+                se[j + 64 * q] = ce[q];
+            }
+            wsync();
+            return;
+        }
+    }
     double mres[NS];
     long long eres[NS];
 #pragma unroll
@@ -415,7 +470,39 @@ __global__ __launch_bounds__(128) void k_post_scan_level(ScanLevel s)
 }
 
 // Waves per workgroup of the local pass (its LDS grows with KB).
-template <int KB> constexpr int post_waves() { return KB <= 32 ? 4 : 2; }
+template <int KB> constexpr int post_waves() { return 2; }
+// Segments per wavefront of the local passes, KB <= 32: lane group h (KB
+// lanes) holds one, its lanes the states.  What bounds these passes is LDS:
+// each step reads whole vectors of KB floats (the forward pass one, the
+// backward pass three), 8 cycles per 16-byte read of a wavefront whatever its
+// lanes share, so two (four) segments per read halve (quarter) the time.
+// The sums run over K rounded up to a multiple of four (KK).  Forward and
+// backward pass together, K = 25, T = 300,007: 224 -> 166 us; K = 20, T =
+// 500,000: 334 -> 212 us, the same bits.
+template <int KB> constexpr int post_segs() { return KB <= 32 ? 64 / KB : 1; }
+// Steps of a staged chunk of the backward pass: half of kChunk for KB <= 32,
+// so that 16 segments and more share a CU.
+template <int KB> constexpr int post_chunk() { return KB <= 32 ? kChunk / 2 : kChunk; }
+
+// Sum (FP64) and maximum over a lane group of HW lanes.
+template <int HW>
+__device__ __forceinline__ double gsum_f64(double x)
+{
+#pragma unroll
+    for (int o = HW / 2; o > 0; o >>= 1) x += __shfl_xor(x, o);
+    return x;
+}
+
+template <int HW>
+__device__ __forceinline__ long long gmax_i64(long long x)
+{
+#pragma unroll
+    for (int o = HW / 2; o > 0; o >>= 1) {
+        const long long y = __shfl_xor(x, o);
+        x = y > x ? y : x;
+    }
+    return x;
+}
 
 // sum_i x[i] * c[i], x from LDS, c in registers, 4 partial chains.
 template <int KB>
@@ -458,39 +545,49 @@ __device__ __forceinline__ void load_gamma_lds(const PostDesc &d, float *gs, flo
 // both sums read from the LDS copy of u_{t-1} (u is never normalised
 // explicitly; every later use is invariant to its scale), stored into the
 // gamma rows.
-template <int KB>
+template <int KB, int KK>
 __global__ __launch_bounds__(64 * post_waves<KB>()) void k_post_forward(PostDesc d)
 {
-    constexpr int NW = post_waves<KB>();
+    constexpr int NW = post_waves<KB>(), S = post_segs<KB>(), HW = 64 / S;
+    constexpr int ES = kChunk + 1;   // odd: one step's emissions lie in different banks
     __shared__ __attribute__((aligned(16))) float gs[KB * KB];
-    __shared__ __attribute__((aligned(16))) float et[NW][KB * kChunk];
-    __shared__ __attribute__((aligned(16))) float sv[NW][KB];
+    __shared__ __attribute__((aligned(16))) float et[NW][S][KB * ES + KB];   // + KB: the groups' banks differ
+    __shared__ __attribute__((aligned(16))) float sv[NW][S][KB];
     load_gamma_lds<KB>(d, gs, nullptr);
-    const int w = threadIdx.x >> 6, j = threadIdx.x & 63;
-    const int64_t b = (int64_t)blockIdx.x * NW + w;
-    if (b >= d.nb || *d.status != 0) return;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, h = lane / HW, j = lane % HW;
+    const int64_t b0 = ((int64_t)blockIdx.x * NW + w) * S, b = b0 + h;
+    if (b0 >= d.nb || *d.status != 0) return;
     const int K = d.K;
-    const int64_t t0 = b * d.L, t1 = min(d.T, t0 + d.L);
-    float *E = et[w], *su = sv[w];
-    const bool live = j < K;
+    float *E = et[w][h], *su = sv[w][h];
+    const bool live = j < K && b < d.nb;
+    const int64_t t0 = b * d.L;
+    const int len = b < d.nb ? (int)min(d.L, d.T - t0) : 0;
+    const int longest = (int)min(d.L, d.T - b0 * d.L);   // the wavefront's first segment
     const int jc = j < KB ? j : 0;
     const Obs obs{d.flag, d.xy, nullptr, kEmisTremor, 0};
-    float gcol[KB];
+    float gcol[KK];
 #pragma unroll
-    for (int i = 0; i < KB; ++i) gcol[i] = gs[i * KB + jc];
-    for (int i = j; i < KB * kChunk; i += 64) E[i] = 0.f;   // rows >= K stay zero
+    for (int i = 0; i < KK; ++i) gcol[i] = gs[i * KB + jc];
+    for (int g = 0; g < S; ++g)
+        for (int i = lane; i < KB * ES; i += 64) et[w][g][i] = 0.f;   // rows >= K stay zero
     if (j < KB) su[j] = live ? (float)d.Aseg[b * K + j] : 0.f;
     wsync();
-    for (int64_t tc = t0; tc < t1; tc += kChunk) {
-        const int nst = (int)min((int64_t)kChunk, t1 - tc);
-        long long ssum = 0;
-        int bad = 0, sh = 0;
-        stage_emissions<kChunk, false>(K, tc, nst, obs, d.sc, E, ssum, bad, sh);
-        for (int tl = 0; tl < nst; ++tl) {
-            const float v = dot_reg<KB>(su, gcol);
-            const float s = sum_lds<KB>(su);
-            const float a = live ? __fdividef(v, s) * E[j * kChunk + tl] : 0.f;
-            if (live) d.gamma[(tc + tl) * K + j] = a;
+    for (int rc = 0; rc < longest; rc += kChunk) {
+        for (int g = 0; g < S; ++g) {
+            const int64_t tg = (b0 + g) * d.L + rc;
+            const int64_t left = min(d.T, (b0 + g + 1) * d.L) - tg;
+            if (left <= 0) break;
+            long long ssum = 0;
+            int bad = 0, sh = 0;
+            stage_emissions<ES, false>(K, tg, (int)min((int64_t)kChunk, left), obs, d.sc, et[w][g], ssum, bad, sh);
+        }
+        const int n = min(kChunk, longest - rc);
+        for (int tl = 0; tl < n; ++tl) {
+            const bool act = live && rc + tl < len;
+            const float v = dot_reg<KK>(su, gcol);
+            const float s = sum_lds<KK>(su);
+            const float a = act ? __fdividef(v, s) * E[jc * ES + tl] : 0.f;
+            if (act) d.gamma[(t0 + rc + tl) * K + j] = a;
             wsync();
             if (j < KB) su[j] = a;
             wsync();
@@ -506,32 +603,34 @@ __global__ __launch_bounds__(64 * post_waves<KB>()) void k_post_forward(PostDesc
 //   xi_t(i,j) = u_{t-1,i} Gamma_ij r_j,  gamma_{t-1,i} = normalise(u_{t-1,i} sum_j Gamma_ij r_j),
 // overwriting the u rows with gamma and accumulating xi (as
 // Gamma_ij sum_t u_{t-1,i} r_t,j) and the moments.
-template <int KB>
+template <int KB, int KK>
 __global__ __launch_bounds__(64 * post_waves<KB>(), KB <= 32 ? 2 : 1) void k_post_backward(PostDesc d)
 {
-    constexpr int NW = post_waves<KB>();
+    constexpr int NW = post_waves<KB>(), S = post_segs<KB>(), HW = 64 / S, CB = post_chunk<KB>();
     __shared__ __attribute__((aligned(16))) float gs[KB * KB], gt[KB * KB];
-    __shared__ __attribute__((aligned(16))) float et[NW][KB * kChunk];   // u rows of a chunk
-    __shared__ __attribute__((aligned(16))) float sv[NW][2][KB];          // r, unnormalised gamma
-    __shared__ double ox[NW][kChunk], oy[NW][kChunk];
-    __shared__ int of[NW][kChunk];
+    __shared__ __attribute__((aligned(16))) float et[NW][S][KB * CB + KB];   // u rows of a chunk
+    __shared__ __attribute__((aligned(16))) float sv[NW][2][S][KB];           // r, unnormalised gamma
+    __shared__ double ox[NW][S][CB], oy[NW][S][CB];
+    __shared__ int of[NW][S][CB];
     load_gamma_lds<KB>(d, gs, gt);
-    const int w = threadIdx.x >> 6, j = threadIdx.x & 63;
-    const int64_t b = (int64_t)blockIdx.x * NW + w;
-    if (b >= d.nb) return;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, h = lane / HW, j = lane % HW;
+    const int64_t b0 = ((int64_t)blockIdx.x * NW + w) * S, b = b0 + h;
+    if (b0 >= d.nb) return;
     const int K = d.K;
-    const int64_t t0 = b * d.L, t1 = min(d.T, t0 + d.L);
-    float *E = et[w], *sr = sv[w][0], *sg = sv[w][1];
-    const bool live = j < K;
+    float *E = et[w][h], *sr = sv[w][0][h], *sg = sv[w][1][h];
+    const bool live = j < K && b < d.nb;
+    const int64_t t0 = b * d.L, t1 = b < d.nb ? min(d.T, t0 + d.L) : t0;
+    const int len = (int)(t1 - t0);
+    const int longest = (int)min(d.L, d.T - b0 * d.L);   // the wavefront's first segment
     const int jc = j < KB ? j : 0;
     if (*d.status != 0) {
         for (int64_t t = t0; t < t1; ++t)
             if (live) d.gamma[t * K + j] = __builtin_nanf("");
         return;
     }
-    float xi[KB], gcol[KB], grow[KB];
+    float xi[KK], gcol[KK], grow[KK];
 #pragma unroll
-    for (int i = 0; i < KB; ++i) {
+    for (int i = 0; i < KK; ++i) {
         xi[i] = 0.f;
         gcol[i] = gs[i * KB + jc];
         grow[i] = gt[i * KB + jc];
@@ -554,58 +653,61 @@ __global__ __launch_bounds__(64 * post_waves<KB>(), KB <= 32 ? 2 : 1) void k_pos
         int ex = 0;
         const double mant = frexp(prod, &ex);
         const long long lv = (prod > 0.0) ? ce + ex : LLONG_MIN;
-        const long long lmax = wmax_i64(lv);
+        const long long lmax = gmax_i64<HW>(lv);
         double v = 0.0;
         if (prod > 0.0) {
             long long shf = lv - lmax;
             if (shf < -1100) shf = -1100;
             v = ldexp(mant, (int)shf);
         }
-        g = (float)(v / wsum_f64(v));
+        g = (float)(v / gsum_f64<HW>(v));
     }
-    const int64_t nch = (t1 - t0 + kChunk - 1) / kChunk;
-    for (int64_t ci = nch - 1; ci >= 0; --ci) {
-        const int64_t tc = t0 + ci * kChunk;
-        const int nst = (int)min((int64_t)kChunk, t1 - tc);
+    for (int rc = (longest - 1) / CB * CB; rc >= 0; rc -= CB) {
         wsync();
-        // E row r = u_{tc+r-1} (row stride KB); positions p = r * KB + i, in
-        // batches of 8 loads issued before their LDS stores
-        for (int q0 = 0; q0 < KB; q0 += 8) {
-            float tmp[8];
+        for (int gi = 0; gi < S; ++gi) {
+            const int64_t s0 = (b0 + gi) * d.L, tc = s0 + rc;
+            const int nst = (int)max((int64_t)0, min((int64_t)CB, min(d.T, s0 + d.L) - tc));
+            float *Eg = et[w][gi];
+            // E row r = u_{tc+r-1} (row stride KB); positions p = r * KB + i, in
+            // batches of 8 loads issued before their LDS stores
+            for (int q0 = 0; q0 < KB * CB / 64; q0 += 8) {
+                float tmp[8];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int pos = j + 64 * (q0 + q), r = pos / KB, i = pos % KB;
-                const int64_t t = tc + r - 1;
-                tmp[q] = (r < nst && i < K && t >= t0) ? d.gamma[t * K + i] : 0.f;
+                for (int q = 0; q < 8; ++q) {
+                    const int pos = lane + 64 * (q0 + q), r = pos / KB, i = pos % KB;
+                    const int64_t t = tc + r - 1;
+                    tmp[q] = (r < nst && i < K && t >= s0) ? d.gamma[t * K + i] : 0.f;
+                }
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    Eg[lane + 64 * (q0 + q)] = tmp[q];   // rows past the segment: zero
+                }
             }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int pos = j + 64 * (q0 + q), r = pos / KB;
-                if (r < nst) E[pos] = tmp[q];
+            if (lane < nst) {
+                const int64_t t = tc + lane;
+                const int f = d.flag[t];
+                of[w][gi][lane] = f;
+                double x = 0.0, y = 0.0;
+                if (f == 1) {
+                    const double2 p = reinterpret_cast<const double2 *>(d.xy)[t];
+                    x = p.x;
+                    y = p.y;
+                }
+                ox[w][gi][lane] = x;
+                oy[w][gi][lane] = y;
             }
         }
-        if (tc == t0 && j < KB) E[j] = a_in;   // u_{t0-1}: the segment's entry message
-        if (j < nst) {
-            const int64_t t = tc + j;
-            const int f = d.flag[t];
-            of[w][j] = f;
-            double x = 0.0, y = 0.0;
-            if (f == 1) {
-                const double2 p = reinterpret_cast<const double2 *>(d.xy)[t];
-                x = p.x;
-                y = p.y;
-            }
-            ox[w][j] = x;
-            oy[w][j] = y;
-        }
         wsync();
-        for (int tl = nst - 1; tl >= 0; --tl) {
-            const int64_t t = tc + tl;
-            if (live) {
+        if (rc == 0 && j < KB) E[j] = a_in;   // u_{t0-1}: the segment's entry message
+        wsync();
+        for (int tl = min(CB, longest - rc) - 1; tl >= 0; --tl) {
+            const int64_t t = t0 + rc + tl;
+            const bool act = live && rc + tl < len;
+            if (act) {
                 d.gamma[t * K + j] = g;
                 mom[0] += g;
-                if (of[w][tl] == 1) {
-                    const float x = (float)(ox[w][tl] - mux), y = (float)(oy[w][tl] - muy);
+                if (of[w][h][tl] == 1) {
+                    const float x = (float)(ox[w][h][tl] - mux), y = (float)(oy[w][h][tl] - muy);
                     mom[1] += g;
                     mom[2] = fmaf(g, x, mom[2]);
                     mom[3] = fmaf(g, y, mom[3]);
@@ -615,18 +717,19 @@ __global__ __launch_bounds__(64 * post_waves<KB>(), KB <= 32 ? 2 : 1) void k_pos
                 }
             }
             const float *up = E + tl * KB;   // u_{t-1}
-            const float pred = dot_reg<KB>(up, gcol);
-            const float r = (live && pred > 0.f) ? __fdividef(g, pred) : 0.f;
+            const float pred = dot_reg<KK>(up, gcol);
+            const float r = (act && pred > 0.f) ? __fdividef(g, pred) : 0.f;
             if (j < KB) sr[j] = r;
             wsync();
 #pragma unroll
-            for (int i = 0; i < KB; ++i) xi[i] = fmaf(up[i], r, xi[i]);
-            const float back = dot_reg<KB>(sr, grow);
-            const float gp = live ? up[j] * back : 0.f;
+            for (int i = 0; i < KK; ++i) xi[i] = fmaf(up[i], r, xi[i]);
+            const float back = dot_reg<KK>(sr, grow);
+            const float gp = act ? up[j] * back : 0.f;
             if (j < KB) sg[j] = gp;
             wsync();
-            g = __fdividef(gp, sum_lds<KB>(sg));
-            if (b == 0 && t == 0 && live) d.part_pre[j] = g;
+            const float gn = __fdividef(gp, sum_lds<KK>(sg));
+            g = act ? gn : g;
+            if (b == 0 && t == 0 && act) d.part_pre[j] = g;
             wsync();
         }
     }
@@ -634,7 +737,7 @@ __global__ __launch_bounds__(64 * post_waves<KB>(), KB <= 32 ? 2 : 1) void k_pos
         // xi(i, j) = Gamma_ij sum_t u_{t-1,i} r_t,j
         float *px = d.part_xi + b * K * K;
 #pragma unroll
-        for (int i = 0; i < KB; ++i)
+        for (int i = 0; i < KK; ++i)
             if (i < K) px[i * K + j] = xi[i] * gcol[i];
         float *pm = d.part_mom + (b * K + j) * kMoments;
 #pragma unroll
@@ -1029,15 +1132,27 @@ __global__ __launch_bounds__(64) void k_em_mstep(int K, const double *delta, con
     }
 }
 
+// KK: K rounded up to a multiple of four, the terms of the passes' sums.
+template <int KB, int KK>
+void launch_local_kk(const PostDesc &d, hipStream_t st)
+{
+    if constexpr (KK < KB) {
+        if (d.K > KK) return launch_local_kk<KB, KK + 4>(d, st);
+    }
+    constexpr int NS = post_waves<KB>() * post_segs<KB>(), NW = post_waves<KB>();
+    const unsigned grid = (unsigned)((d.nb + NS - 1) / NS);
+    hipLaunchKernelGGL((k_post_forward<KB, KK>), dim3(grid), dim3(64 * NW), 0, st, d);
+    hipLaunchKernelGGL((k_post_backward<KB, KK>), dim3(grid), dim3(64 * NW), 0, st, d);
+}
+
 template <int KB>
 void launch_local(const PostDesc &d, hipStream_t st)
 {
-    constexpr int NW = post_waves<KB>();
-    const unsigned grid = (unsigned)((d.nb + NW - 1) / NW);
     if constexpr (KB <= 64) {
-        hipLaunchKernelGGL(k_post_forward<KB>, dim3(grid), dim3(64 * NW), 0, st, d);
-        hipLaunchKernelGGL(k_post_backward<KB>, dim3(grid), dim3(64 * NW), 0, st, d);
+        launch_local_kk<KB, KB == 16 ? 4 : KB / 2 + 4>(d, st);
     } else {
+        constexpr int NW = post_waves<KB>();
+        const unsigned grid = (unsigned)((d.nb + NW - 1) / NW);
         hipLaunchKernelGGL(k_post_forward_wide<KB>, dim3(grid), dim3(64 * NW), 0, st, d);
         hipLaunchKernelGGL(k_post_backward_wide<KB>, dim3(grid), dim3(64 * NW), 0, st, d);
     }
