@@ -2,13 +2,14 @@
 
 Workload: K = 25 hidden states, T = 1,000,000 observations, one parameter set
 (synthetic tremor-shaped data, seed 1).  One step = one full evaluation of
-ln L (eq. 2) with the blocked FP32 MFMA path: parameter preparation, fused
-emission + segment products, and the combination tree down to ln L.  Inputs
-are resident in HBM before timing starts.
+ln L (eq. 2) with the blocked FP32 MFMA path: parameter preparation, the
+segment chains (fused emissions, verified forward vectors), and the guarded
+product path behind them, which returns at once where the chains have served
+the call.  Inputs are resident in HBM before timing starts.
 
 Reported beside it: the plain forward recursion (Algorithm 1) on the GPU, the
 error of both against the FP64 CPU oracle, the roofline position of the
-dominant kernel (segment products; algorithmic flops 2*K^3 per observation,
+dominant kernel (segment chains; algorithmic flops 2*K^2 per observation,
 FP32 MFMA peak), and the oracle's own throughput on the host cores.
 
     python bench.py [--gpus 1] [--steps 200] [--warmup 10]
@@ -41,12 +42,12 @@ if ROOT not in sys.path:
 PEAK_FP32_MFMA_TFLOPS = 157.3  # MI355X dense FP32 matrix peak
 PEAK_16BIT_MFMA_TFLOPS = 2500.0  # MI355X dense BF16 / FP16 matrix peak
 PEAK_HBM_GBS = 8000.0
-COUNTERS = os.path.join(ROOT, "profiles", "k_blocked_k25_t1e6_counters.txt")
+COUNTERS = os.path.join(ROOT, "profiles", "k_chain_k25_t1e6_counters.txt")
 
 
-# The sources the segment kernel of the K=25 workload is built from (its
+# The sources the chain kernel of the K=25 workload is built from (its
 # translation unit and the headers it includes).
-SEGMENT_KERNEL_SOURCES = ("hmm_device.hpp", "hmm_kernels.hpp", "hmm_host.hpp", "hmm_api.hip")
+SEGMENT_KERNEL_SOURCES = ("hmm_device.hpp", "hmm_kernels.hpp", "hmm_chain.hpp", "hmm_host.hpp", "hmm_chain.hip")
 
 
 def kernel_sources_sha256():
@@ -77,46 +78,28 @@ def measured_traffic():
     return int(round(fetch + write))
 
 
-def issued_mfma_flops(K, T, n_blocks):
-    """Flops the FP32 segment kernel issues on the matrix cores for one
-    evaluation: per observation MT^2 output tiles x NSL live contraction slots
-    x the flops of one MFMA (32x32x2: 4096, 16x16x4: 2048), plus the W - 1
-    products of each workgroup's tree.  Mirrors the library's tile choice
-    (side S, MT tiles per side, W wavefronts per workgroup)."""
-    if K <= 16:
-        S, MT = 16, 1
-    elif K <= 32:
-        S, MT = 32, 1
-    elif K <= 48:
-        S, MT = 16, 3
-    elif K <= 64:
-        S, MT = 32, 2
-    else:
-        S, MT = 16, 5
-    KP = S * MT
-    W = 16 if KP <= 32 else (12 if KP <= 48 else (8 if KP <= 64 else 4))
-    RS, G = S * S // 64, 64 // S
-    nsl = min(MT * RS, -(-K // G))   # slot-major state order: ceil(K / G) live slots
-    per_mfma = 2 * S * S * (64 // S)
-    per_product = MT * MT * nsl * per_mfma
-    NT = {19: 5, 20: 5, 22: 5, 21: 2}.get(K, 4)
-    waves_per_wg = 16 if NT == 2 else 8
-    G = 32 * NT // K
-    if 16 < K <= 25 and T >= 16 * 256 * waves_per_wg * G:
-        # packed (the default per-K table of a single set, for a sequence that
-        # fills every CU at 16-step segments): G = 32 NT // K segments per
-        # wavefront share NT column tiles (5 for K 19, 20, 22, 2 for K 21,
-        # else 4); every wavefront runs ceil(T / n_blocks) steps (balanced
-        # segment lengths) of NT * NSL MFMAs, then folds its G products, and the
-        # wavefronts of a workgroup (16 for NT = 2, else 8) meet in the tree
-        steps = -(-T // n_blocks) if n_blocks else 0
-        waves = -(-n_blocks // G)
-        n_wg = -(-waves // waves_per_wg)
-        issued = (waves * steps * NT * per_product + n_blocks * per_product
-                  + n_wg * (waves_per_wg - 1) * per_product)
-        return float(issued), {"S": S, "MT": MT, "NSL": nsl, "packed_segments_per_wave": G, "packed_tiles": NT}
-    n_wg = -(-n_blocks // W)
-    return float(T * per_product + n_wg * (W - 1) * per_product), {"S": S, "MT": MT, "NSL": nsl}
+def chain_flops(K, T):
+    """Algorithmic flops of one evaluation by the segment chains: a
+    vector-matrix product per observation."""
+    return 2.0 * T * K ** 2
+
+
+def issued_chain_flops(K, T, Gamma):
+    """Flops the chain kernel issues on the matrix cores for one evaluation:
+    a wavefront walks 16 segments as the columns of 16x16x4 MFMAs (2048 flops
+    each), ceil(K/16) row tiles x ceil(K/4) contraction slots per step, over
+    its segments' observations and the warm-up before them.  Mirrors the
+    library's segment count and warm-up."""
+    big = T >= (400_000 if K <= 32 else 1_250_000)
+    walkers = (2 if big else 1) if K <= 32 else (4 if big else 2)
+    L = max(32, -(-T // (256 * 16 * walkers)))
+    nb = -(-T // L)
+    stay = min(max(float(Gamma.diagonal().max()), 1e-3), 1.0 - 1e-12)
+    warm = min(max(4 * math.ceil(4.25 / -math.log(stay)), 40), 112)
+    tiles, slots = -(-K // 16), -(-K // 4)
+    steps = 4 * -(-(-(-T // nb) + warm) // 4)
+    return float(-(-nb // 16) * steps * tiles * slots * 2048), {"MT": tiles, "NSL": slots, "pairs": walkers,
+                                                               "segments": nb, "warm_up": warm}
 
 
 def host_cpu():
@@ -243,18 +226,17 @@ def main():
         ll_serial = float(out.item())
         serial_evals_per_s = args.serial_steps / (s1 - s0)
 
-    # ---- roofline of the dominant kernel (segment products)
-    flops = 2.0 * T * K ** 3                 # algorithmic, unpadded
-    issued, tile = issued_mfma_flops(K, T, plan["n_blocks"])
+    # ---- roofline of the dominant kernel (segment chains)
+    flops = chain_flops(K, T)                # algorithmic, unpadded
+    issued, shape = issued_chain_flops(K, T, prm.Gamma)
     achieved_tflops = flops / (kern_avg_ms * 1e-3) / 1e12
     roofline = {"bound": "mfma", "achieved": round(achieved_tflops, 3),
                 "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(achieved_tflops / PEAK_FP32_MFMA_TFLOPS, 4),
                 "traffic": measured_traffic(), "traffic_unit": "bytes/launch",
                 "algorithmic_bytes": 17 * T,
-                "kernel": ("k_blocked_packed<%d,%d,%d>" % (tile["packed_tiles"], tile["packed_segments_per_wave"],
-                                                             tile["NSL"]) if "packed_tiles" in tile
-                           else "k_blocked<%d,%d,%d>" % (tile["S"], tile["MT"], tile["NSL"])),
+                "kernel": "k_chain<%d,%d>" % (shape["MT"], shape["NSL"]),
+                "segments": shape["segments"], "warm_up": shape["warm_up"],
                 "kernel_avg_ms": round(kern_avg_ms, 5),
                 "launches_timed": launches, "flops_per_launch": flops,
                 "issued_flops_per_launch": issued,
@@ -355,10 +337,9 @@ def bench_k80(args):
     ctx = binding.Context(0)
     d = binding.to_device(prm, obs)
     out = torch.empty(1, dtype=torch.float64, device="cuda")
-    flops = 2.0 * T * K ** 3
     res = {}
-    # the *_split forms carry the transition matrix as two 16-bit parts (twice
-    # the matrix-core work); their flops are still counted once (algorithmic)
+    # algorithmic flops: the FP32 path's chains take 2 K^2 per observation, the
+    # 16-bit segment products 2 K^3; the *_split forms carry the transition matrix as two 16-bit parts (twice the matrix-core work), counted once
     for algo, peak in (("blocked_f32", PEAK_FP32_MFMA_TFLOPS), ("blocked_bf16", PEAK_16BIT_MFMA_TFLOPS),
                        ("blocked_f16", PEAK_16BIT_MFMA_TFLOPS), ("blocked_bf16_split", PEAK_16BIT_MFMA_TFLOPS),
                        ("blocked_f16_split", PEAK_16BIT_MFMA_TFLOPS)):
@@ -368,6 +349,7 @@ def bench_k80(args):
         n, ms = ctx.profile_read()
         ctx.profile(False)
         kern = ms / max(n, 1) * 1e-3
+        flops = chain_flops(K, T) if algo == "blocked_f32" else 2.0 * T * K ** 3
         ll = float(out.item())
         res[algo] = {"evals_per_s": round(1.0 / sec, 3), "ms_per_eval": round(sec * 1e3, 3),
                      "segment_kernel_ms": round(kern * 1e3, 3),
@@ -389,7 +371,7 @@ def bench_batch(args):
     n = len(sets)
     ctx = binding.Context(0)
     d = binding.batch_to_device(packed)
-    flops = float(sum(2.0 * obs.T * prm.K ** 3 for prm, obs in sets))
+    flops = float(sum(chain_flops(prm.K, obs.T) for prm, obs in sets))
     obs_total = int(packed["T"].sum())
     chosen = ctx.autotune_batched(**d, reps=1)
     out = ctx.loglik_batched(**d)
@@ -456,7 +438,7 @@ def bench_chains(args):
     sets of K=25 over T=105,000 observations (seed 6, the size of the paper's
     Shikoku record).  One batched call (captured graph) vs the same sets as
     sequential single-set calls; per-call HIP-event medians; algorithmic
-    rate n * 2*T*K^3 flops against the FP32 MFMA peak."""
+    rate n * 2*T*K^2 flops against the FP32 MFMA peak."""
     import numpy as np
     import torch
     from paper_2003_03508_amd import binding, synth
@@ -501,7 +483,7 @@ def bench_chains(args):
         steps = max(20, args.steps // 4)
         mb = median_ms(batched, steps, 3)
         ms = median_ms(sequential, steps, 2)
-        flops = n * 2.0 * T * K ** 3
+        flops = n * chain_flops(K, T)
         rb, rs = out.cpu().numpy(), outs.cpu().numpy()
         res[name] = {"sets": n, "K": K, "T": T,
                      "batched_ms": round(mb, 4), "sequential_ms": round(ms, 4),
@@ -519,7 +501,7 @@ def bench_kinds(args):
     """Other emission models through the same kernels: Poisson counts and a
     1-D Gaussian, K=25, T=1e6 (synthetic, seeds 301 / 302): blocked FP32 vs the
     plain forward recursion vs the FP64 oracle, and the segment kernel's
-    MFMA roofline (2*T*K^3 algorithmic flops)."""
+    MFMA roofline (2*T*K^2 algorithmic flops)."""
     import torch
     from paper_2003_03508_amd import binding, synth
     import oracle
@@ -547,7 +529,7 @@ def bench_kinds(args):
         want = oracle.loglik_kind(kind, ks.delta, ks.Gamma, ks.e0, ks.e1, ks.obs)
         c1 = time.perf_counter()
         kern = ms / max(n, 1) * 1e-3
-        flops = 2.0 * T * K ** 3
+        flops = chain_flops(K, T)
         res[name] = {"evals_per_s": round(1.0 / sec, 2), "ms_per_eval": round(sec * 1e3, 4),
                      "plain_forward_evals_per_s": round(1.0 / sec_s, 3),
                      "speedup_vs_plain_forward": round(sec_s / sec, 1),
@@ -567,7 +549,7 @@ def bench_twalk(args):
     given T=105,000 observations (the size of the paper's Shikoku record;
     synthetic, seed 6), one exact FP32 likelihood per chain and iteration.
     Iterations/s of one chain (the paper's setting) and of many chains
-    batched; the iteration's algorithmic rate (chains * 2*T*K^3 flops per
+    batched; the iteration's algorithmic rate (chains * 2*T*K^2 flops per
     iteration) against the FP32 MFMA peak; the FP64 oracle's t-walk on one
     host thread."""
     import numpy as np
@@ -588,7 +570,7 @@ def bench_twalk(args):
     rng = np.random.default_rng(7)
     f64 = lambda a: torch.as_tensor(np.ascontiguousarray(a), dtype=torch.float64, device="cuda")
     spread = 1e-3 * (np.abs(th0) + 1.0)
-    flops_eval = 2.0 * T * K ** 3
+    flops_eval = chain_flops(K, T)
     res = {}
     for C, n_iter in ((1, max(500, args.steps * 5)), (args.twalk_chains, max(100, args.steps))):
         ch = binding.Chains(ctx, K, C, d["flag"], d["xy"], box, seed=11, history=64)
