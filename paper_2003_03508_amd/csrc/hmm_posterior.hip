@@ -477,8 +477,10 @@ template <int KB> constexpr int post_waves() { return 2; }
 // backward pass three), 8 cycles per 16-byte read of a wavefront whatever its
 // lanes share, so two (four) segments per read halve (quarter) the time.
 // The sums run over K rounded up to a multiple of four (KK).  Forward and
-// backward pass together, K = 25, T = 300,007: 224 -> 166 us; K = 20, T =
-// 500,000: 334 -> 212 us, the same bits.
+// backward pass together, K = 25, T = 300,007: 224 -> 140 us; K = 20, T =
+// 500,000: 334 -> 173 us, the same bits.  The forward pass stages the emissions
+// of all its segments at once, every lane an observation, four states' constants
+// a load (70 -> 57 us, K = 25).
 template <int KB> constexpr int post_segs() { return KB <= 32 ? 64 / KB : 1; }
 // Steps of a staged chunk of the backward pass: half of kChunk for KB <= 32,
 // so that 16 segments and more share a CU.
@@ -549,7 +551,7 @@ template <int KB, int KK>
 __global__ __launch_bounds__(64 * post_waves<KB>()) void k_post_forward(PostDesc d)
 {
     constexpr int NW = post_waves<KB>(), S = post_segs<KB>(), HW = 64 / S;
-    constexpr int ES = kChunk + 1;   // odd: one step's emissions lie in different banks
+    constexpr int ES = HW + 1;   // steps of a chunk; odd: one step's emissions lie in different banks
     __shared__ __attribute__((aligned(16))) float gs[KB * KB];
     __shared__ __attribute__((aligned(16))) float et[NW][S][KB * ES + KB];   // + KB: the groups' banks differ
     __shared__ __attribute__((aligned(16))) float sv[NW][S][KB];
@@ -564,24 +566,44 @@ __global__ __launch_bounds__(64 * post_waves<KB>()) void k_post_forward(PostDesc
     const int len = b < d.nb ? (int)min(d.L, d.T - t0) : 0;
     const int longest = (int)min(d.L, d.T - b0 * d.L);   // the wavefront's first segment
     const int jc = j < KB ? j : 0;
-    const Obs obs{d.flag, d.xy, nullptr, kEmisTremor, 0};
     float gcol[KK];
 #pragma unroll
     for (int i = 0; i < KK; ++i) gcol[i] = gs[i * KB + jc];
-    for (int g = 0; g < S; ++g)
-        for (int i = lane; i < KB * ES; i += 64) et[w][g][i] = 0.f;   // rows >= K stay zero
     if (j < KB) su[j] = live ? (float)d.Aseg[b * K + j] : 0.f;
     wsync();
-    for (int rc = 0; rc < longest; rc += kChunk) {
-        for (int g = 0; g < S; ++g) {
-            const int64_t tg = (b0 + g) * d.L + rc;
-            const int64_t left = min(d.T, (b0 + g + 1) * d.L) - tg;
-            if (left <= 0) break;
-            long long ssum = 0;
-            int bad = 0, sh = 0;
-            stage_emissions<ES, false>(K, tg, (int)min((int64_t)kChunk, left), obs, d.sc, et[w][g], ssum, bad, sh);
+    // lane (h, j): observation j of the chunk of segment h, the next chunk's in flight
+    const int64_t tf = b < d.nb ? t0 : 0;
+    uint8_t flag;
+    double2 xy;
+    auto fetch = [&](int rc) {
+        const int64_t t = min(tf + rc + j, d.T - 1);
+        flag = d.flag[t];
+        xy = reinterpret_cast<const double2 *>(d.xy)[t];
+    };
+    fetch(0);
+    for (int rc = 0; rc < longest; rc += HW) {
+        // emissions as stage_emissions rounds them (rows j < K; invalid data
+        // does not come here)
+        const bool tremor = flag == 1;
+        const double x = xy.x, y = xy.y;
+        fetch(rc + HW);
+        double m = -INFINITY;
+#pragma unroll 4
+        for (int k = 0; k < K; ++k) m = fmax(m, state_log2_emission(d.sc[k], tremor, x, y));
+        int sh = 0;
+        if (m > -1.0e9 && m < 1.0e9) sh = (int)floor(m) - kEmisBias;
+#pragma unroll 4
+        for (int k = 0; k < K; ++k) {
+            const double r = state_log2_emission(d.sc[k], tremor, x, y) - (double)sh;
+            float e = 0.f;
+            if (r > -160.0) {
+                const double f = floor(r);
+                e = __builtin_amdgcn_ldexpf(exp2f((float)(r - f)), (int)f);
+            }
+            E[k * ES + j] = e;
         }
-        const int n = min(kChunk, longest - rc);
+        wsync();
+        const int n = min(HW, longest - rc);
         for (int tl = 0; tl < n; ++tl) {
             const bool act = live && rc + tl < len;
             const float v = dot_reg<KK>(su, gcol);
@@ -980,29 +1002,42 @@ __global__ __launch_bounds__(64 * post_waves<KB>()) void k_post_backward_wide(Po
 // chunk partials in order.
 constexpr int kSumChunks = 64;
 
-__global__ __launch_bounds__(256) void k_colsum_partial(const float *__restrict__ in, int64_t rows, int64_t n,
-                                                        double *__restrict__ part)
+// Two sets of columns in one launch (xi and the moments): blocks from split on
+// take the second.
+struct ColSums {
+    const float *in[2];
+    int64_t n[2];
+    double *part[2], *out[2];
+    int64_t rows;
+    int split[2];   // of the partial sums (64 columns a block), of the final ones (256)
+};
+
+__global__ __launch_bounds__(256) void k_colsum_partial(ColSums a)
 {
     __shared__ double red[4][64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t col = blockIdx.x * 64 + lane;
+    const int q = (int)blockIdx.x >= a.split[0] ? 1 : 0;
+    const float *in = a.in[q];
+    const int64_t n = a.n[q], rows = a.rows;
+    const int64_t col = ((int)blockIdx.x - (q ? a.split[0] : 0)) * 64 + lane;
     const int64_t c = blockIdx.y;
     double s = 0.0;
     if (col < n)
         for (int64_t r = c + (int64_t)w * kSumChunks; r < rows; r += 4 * kSumChunks) s += (double)in[r * n + col];
     red[w][lane] = s;
     __syncthreads();
-    if (w == 0 && col < n) part[c * n + col] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+    if (w == 0 && col < n) a.part[q][c * n + col] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
 }
 
-__global__ __launch_bounds__(256) void k_colsum_final(const double *__restrict__ part, int64_t n,
-                                                      double *__restrict__ out)
+__global__ __launch_bounds__(256) void k_colsum_final(ColSums a)
 {
-    const int64_t col = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int q = (int)blockIdx.x >= a.split[1] ? 1 : 0;
+    const int64_t n = a.n[q];
+    const int64_t col = ((int)blockIdx.x - (q ? a.split[1] : 0)) * 256 + threadIdx.x;
     if (col >= n) return;
     double s = 0.0;
-    for (int c = 0; c < kSumChunks; ++c) s += part[(int64_t)c * n + col];
-    out[col] = s;
+    for (int c = 0; c < kSumChunks; ++c) s += a.part[q][(int64_t)c * n + col];
+    a.out[q][col] = s;
 }
 
 // stats = [xi (K*K) | pre (K) | moments (K*7)] from the column sums of the
@@ -1184,11 +1219,13 @@ int64_t post_segments(const hmm_ctx *ctx, const KernelSet &ks)
     return (int64_t)per_cu * n_cu;
 }
 
-void launch_colsum(const float *in, int64_t rows, int64_t n, double *part, double *out, hipStream_t st)
+void launch_colsums(ColSums a, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_colsum_partial, dim3((unsigned)((n + 63) / 64), kSumChunks), dim3(256), 0, st, in, rows, n,
-                       part);
-    hipLaunchKernelGGL(k_colsum_final, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part, n, out);
+    a.split[0] = (int)((a.n[0] + 63) / 64);
+    a.split[1] = (int)((a.n[0] + 255) / 256);
+    hipLaunchKernelGGL(k_colsum_partial, dim3((unsigned)(a.split[0] + (a.n[1] + 63) / 64), kSumChunks), dim3(256), 0,
+                       st, a);
+    hipLaunchKernelGGL(k_colsum_final, dim3((unsigned)(a.split[1] + (a.n[1] + 255) / 256)), dim3(256), 0, st, a);
 }
 
 int posterior_impl(hmm_ctx *ctx, int32_t K, const double *delta, const double *Gamma, const double *p,
@@ -1337,9 +1374,17 @@ int posterior_impl(hmm_ctx *ctx, int32_t K, const double *delta, const double *G
     if (out_stats) {
         double *part = at<double>(ws, o_part);
         if (nb > 0) {
-            launch_colsum(d.part_xi, nb, (int64_t)K * K, part, out_stats, st);
-            launch_colsum(d.part_mom, nb, (int64_t)K * kMoments, part + (size_t)kSumChunks * K * K,
-                          out_stats + K * K + K, st);
+            ColSums cs;
+            cs.in[0] = d.part_xi;
+            cs.in[1] = d.part_mom;
+            cs.n[0] = (int64_t)K * K;
+            cs.n[1] = (int64_t)K * kMoments;
+            cs.part[0] = part;
+            cs.part[1] = part + (size_t)kSumChunks * K * K;
+            cs.out[0] = out_stats;
+            cs.out[1] = out_stats + K * K + K;
+            cs.rows = nb;
+            launch_colsums(cs, st);
         }
         hipLaunchKernelGGL(k_post_finish, dim3(1), dim3(64), 0, st, d, out_stats);
     }
