@@ -828,7 +828,7 @@ __device__ __forceinline__ void blocked_job(const SetDesc &d, const WgJob &job, 
         for (int i = lane; i < KP * kChunk; i += kWave) Et[i] = 0.f;  // rows >= K stay zero
         for (int64_t tc = t0; tc < t1; tc += kChunk) {
             const int nst = (int)min((int64_t)kChunk, t1 - tc);
-            stage_emissions<kChunk, GEN>(K, tc, nst, obs, sc, Et, ssum, bad, sh);
+            stage_emissions<kChunk, GEN, 4>(K, tc, nst, obs, sc, Et, ssum, bad, sh);
             for (int tl = 0; tl < nst; tl += kUnroll<S, MT>) {
                 // scaled emissions of the rows this lane holds, kUnroll steps at once
                 float evu[MT][RS][kUnroll<S, MT>];

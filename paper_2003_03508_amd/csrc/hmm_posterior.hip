@@ -141,7 +141,7 @@ template <int KP> constexpr int msg_ns() { return (KP + 63) / 64; }
 // loops run over all KP padded states with branch-free bodies, so their LDS
 // reads issue back to back: padded states contribute exact zeros (sf = 0,
 // si = LLONG_MIN, zero rows of M).
-template <int KP>
+template <int KP, int KK>
 __device__ void msg_forward(int K, const float *M, const long long *E, double (&a)[msg_ns<KP>()], double *sa,
                             double *sf, long long *si)
 {
@@ -155,7 +155,7 @@ __device__ void msg_forward(int K, const float *M, const long long *E, double (&
     wsync();
     long long emax = LLONG_MIN;
 #pragma unroll
-    for (int i = 0; i < KP; ++i) emax = si[i] > emax ? si[i] : emax;
+    for (int i = 0; i < KK; ++i) emax = si[i] > emax ? si[i] : emax;
 #pragma unroll
     for (int q = 0; q < NS; ++q) {
         const int js = j + 64 * q;
@@ -174,7 +174,7 @@ __device__ void msg_forward(int K, const float *M, const long long *E, double (&
         const int js = j + 64 * q, jc = js < KP ? js : 0;
         double t = 0.0;
 #pragma unroll
-        for (int i = 0; i < KP; ++i) t += sf[i] * (double)M[i * KP + jc];
+        for (int i = 0; i < KK; ++i) t += sf[i] * (double)M[i * KP + jc];
         s[q] = js < K ? t : 0.0;
     }
     wsync();
@@ -183,7 +183,7 @@ __device__ void msg_forward(int K, const float *M, const long long *E, double (&
     wsync();
     double tot = 0.0;
 #pragma unroll
-    for (int i = 0; i < KP; ++i) tot += sa[i];
+    for (int i = 0; i < KK; ++i) tot += sa[i];
 #pragma unroll
     for (int q = 0; q < NS; ++q) {
         const int js = j + 64 * q;
@@ -204,9 +204,9 @@ __device__ void msg_forward(int K, const float *M, const long long *E, double (&
 // scale.  Where the state of the largest ce_j has no zero in its column of M~,
 // h_i is the same for every row and each lane scales its own state once for
 // all (the same bits: a chain of exponent shifts per term and row is what
-// bounds the level otherwise: 36 -> 23 us for 16 products, K = 25).  Lane i < K holds (cm_i, ce_i), mirrored in LDS (sm, se); lanes of
+// bounds the level otherwise: 36 -> 21 us for 16 products, K = 25).  Lane i < K holds (cm_i, ce_i), mirrored in LDS (sm, se); lanes of
 // padded states hold 0, so their terms drop out of the branch-free loops.
-template <int KP>
+template <int KP, int KK>
 __device__ void msg_backward(int K, const float *Mt, const long long *E, double (&cm)[msg_ns<KP>()],
                              long long (&ce)[msg_ns<KP>()], double *sm, long long *se)
 {
@@ -246,7 +246,7 @@ __device__ void msg_backward(int K, const float *Mt, const long long *E, double 
                 const int i = j + 64 * q, ic = i < KP ? i : 0;
                 double sum = 0.0;
 #pragma unroll
-                for (int u = 0; u < KP; ++u) sum += (double)Mt[u * KP + ic] * sm[u];
+                for (int u = 0; u < KK; ++u) sum += (double)Mt[u * KP + ic] * sm[u];
                 int ex = 0;
                 const double m = frexp(sum, &ex);
                 mnew[q] = i < K ? m : 0.0;
@@ -392,7 +392,8 @@ __device__ __forceinline__ void product_store(const ProdRegs<KP> &r, float *lm, 
     wsync();
 }
 
-template <int KP>
+// KK: K rounded up to a multiple of four, the terms of the messages' sums.
+template <int KP, int KK>
 __global__ __launch_bounds__(128) void k_post_scan_level(ScanLevel s)
 {
     constexpr int NS = msg_ns<KP>();
@@ -430,7 +431,7 @@ __global__ __launch_bounds__(128) void k_post_scan_level(ScanLevel s)
             if (c + 1 < c1) {
                 product_store<KP>(nx, lm[0], le[0], false);
                 if (c + 2 < c1) product_load<KP>(s.M + (c + 1) * KP * KP, s.E + (c + 1) * KP, nx);
-                msg_forward<KP>(K, lm[0], le[0], a, sv[0], sf, si);
+                msg_forward<KP, KK>(K, lm[0], le[0], a, sv[0], sf, si);
             }
         }
     } else {
@@ -463,7 +464,7 @@ __global__ __launch_bounds__(128) void k_post_scan_level(ScanLevel s)
             if (c > c0) {
                 product_store<KP>(nx, lm[1], le[1], true);
                 if (c - 1 > c0) product_load<KP>(s.M + (c - 1) * KP * KP, s.E + (c - 1) * KP, nx);
-                msg_backward<KP>(K, lm[1], le[1], cm, ce, sv[1], se);
+                msg_backward<KP, KK>(K, lm[1], le[1], cm, ce, sv[1], se);
             }
         }
     }
@@ -1228,6 +1229,15 @@ void launch_colsums(ColSums a, hipStream_t st)
     hipLaunchKernelGGL(k_colsum_final, dim3((unsigned)(a.split[1] + (a.n[1] + 255) / 256)), dim3(256), 0, st, a);
 }
 
+template <int KP, int KK>
+void launch_scan(const ScanLevel &s, unsigned parents, hipStream_t st)
+{
+    if constexpr (KK < KP) {
+        if (s.K > KK) return launch_scan<KP, KK + 4>(s, parents, st);
+    }
+    hipLaunchKernelGGL((k_post_scan_level<KP, KK>), dim3(parents), dim3(128), 0, st, s);
+}
+
 int posterior_impl(hmm_ctx *ctx, int32_t K, const double *delta, const double *Gamma, const double *p,
                    const double *mu, const double *Sigma, int64_t T, const uint8_t *flag, const double *xy,
                    void *stream, float *gamma, double *stats, double *loglik, bool need_stats_ws,
@@ -1357,11 +1367,11 @@ int posterior_impl(hmm_ctx *ctx, int32_t K, const double *delta, const double *G
             sl.pad = 0;
             const unsigned parents = top ? 1u : (unsigned)cnt[l + 1];
             switch (KP) {
-            case 16: hipLaunchKernelGGL(k_post_scan_level<16>, dim3(parents), dim3(128), 0, st, sl); break;
-            case 32: hipLaunchKernelGGL(k_post_scan_level<32>, dim3(parents), dim3(128), 0, st, sl); break;
-            case 48: hipLaunchKernelGGL(k_post_scan_level<48>, dim3(parents), dim3(128), 0, st, sl); break;
-            case 64: hipLaunchKernelGGL(k_post_scan_level<64>, dim3(parents), dim3(128), 0, st, sl); break;
-            default: hipLaunchKernelGGL(k_post_scan_level<80>, dim3(parents), dim3(128), 0, st, sl); break;
+            case 16: launch_scan<16, 4>(sl, parents, st); break;
+            case 32: launch_scan<32, 20>(sl, parents, st); break;
+            case 48: launch_scan<48, 36>(sl, parents, st); break;
+            case 64: launch_scan<64, 52>(sl, parents, st); break;
+            default: launch_scan<80, 68>(sl, parents, st); break;
             }
         }
         if (K <= 16) launch_local<16>(d, st);
