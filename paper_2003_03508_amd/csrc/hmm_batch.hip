@@ -75,8 +75,9 @@ struct BatchPlan {
     std::vector<BatchClass> classes;
     // captured launch sequence (classes forked onto parallel branches): from
     // the second call with the same descriptors on, the first one launches it
-    // directly (a capture costs more than the launches it saves once).
-    // Streams and events are kept from plan to plan.
+    // directly on the caller's stream (a capture costs more than the launches
+    // it saves once).  The capture's streams and events belong to the plan:
+    // none that a capture has used serves another plan or a direct launch.
     bool launched = false;
     static constexpr int kBranches = 4;
     hipStream_t cap = nullptr;
@@ -665,10 +666,10 @@ int enqueue(const BatchPlan &bp, hipStream_t st, const BatchClass *only = nullpt
     return HMM_OK;
 }
 
-// Streams and events of the branches (and the capture stream), once per context.
-int ensure_branches(BatchPlan &bp)
+// Streams and events of the branches, and the capture stream.
+int make_branches(BatchPlan &bp)
 {
-    if (bp.fork) return HMM_OK;
+    if (bp.fork) return HMM_OK;   // an earlier capture of this plan failed
     if (hipStreamCreateWithFlags(&bp.cap, hipStreamNonBlocking) != hipSuccess) return HMM_E_DEVICE;
     for (int b = 0; b < BatchPlan::kBranches; ++b) {
         if (hipStreamCreateWithFlags(&bp.aux[b], hipStreamNonBlocking) != hipSuccess) return HMM_E_DEVICE;
@@ -680,7 +681,7 @@ int ensure_branches(BatchPlan &bp)
 
 int capture(BatchPlan &bp)
 {
-    if (ensure_branches(bp) != HMM_OK) return HMM_E_DEVICE;
+    if (make_branches(bp) != HMM_OK) return HMM_E_DEVICE;
     if (hipStreamBeginCapture(bp.cap, hipStreamCaptureModeThreadLocal) != hipSuccess) return HMM_E_DEVICE;
     int rc = enqueue(bp, bp.cap, nullptr, bp.classes.size() > 1);
     hipGraph_t g = nullptr;
@@ -750,12 +751,6 @@ int get_plan(hmm_ctx *ctx, int n, const int32_t *K, const int64_t *T, const int6
         std::swap(bp->host, old->host);
         std::swap(bp->host_bytes, old->host_bytes);
         std::swap(bp->copied, old->copied);
-        std::swap(bp->cap, old->cap);
-        std::swap(bp->fork, old->fork);
-        for (int b = 0; b < BatchPlan::kBranches; ++b) {
-            std::swap(bp->aux[b], old->aux[b]);
-            std::swap(bp->join[b], old->join[b]);
-        }
         batch_plan_free(old);
         ctx->batch = nullptr;
     }
@@ -838,9 +833,7 @@ int hmm_loglik_batched(hmm_ctx *ctx, int32_t n, const int32_t *K, const int64_t 
         }
         return HMM_OK;
     }
-    const bool branches = bp->classes.size() > 1 && ctx->batch_graph && !user_capture;
-    if (branches && ensure_branches(*bp) != HMM_OK) return HMM_E_DEVICE;
-    rc = enqueue(*bp, st, nullptr, branches);
+    rc = enqueue(*bp, st);
     if (rc != HMM_OK) return rc;
     bp->launched = true;
     return hipGetLastError() == hipSuccess ? HMM_OK : HMM_E_DEVICE;

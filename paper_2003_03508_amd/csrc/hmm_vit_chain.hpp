@@ -34,8 +34,8 @@
 // issue (K = 25: 100 instructions a step, 160 with the backpointers, of which
 // 50 are the comparisons and selects of the argmax), and a step's chain of
 // LDS round trip, additions and row maxima, 0.37 us, where a SIMD holds only
-// one wavefront.  K = 25, T = 1e6: 1.60 -> 0.36 ms for the call (0.28 without
-// the score's flat vectors), K = 64, T = 105,000: 3.15 -> 0.25 ms.
+// one wavefront.  K = 25, T = 1e6: 1.55 -> 0.33 ms for the call (0.27 without
+// the score's flat vectors), K = 64, T = 105,000: 3.2 -> 0.23 ms.
 #pragma once
 
 #include "hmm_chain.hpp"
@@ -71,7 +71,8 @@ struct VitChain {
     int64_t fnb, fL;         // segments of the product path, their length
     int64_t T, nb, q, r;     // segments of q or (the first r) q + 1 observations
     int K, KB;
-    int rows, cblocks;             // rows: backpointers of a segment, q + 1 + kVitAhead at most
+    int rows;                // of backpointers of a segment: its length + kVitAhead
+    int cblocks;             // workgroups of segments; the first launch's others walk flat vectors
 };
 
 __device__ __forceinline__ float max3_f32(float a, float b, float c)
