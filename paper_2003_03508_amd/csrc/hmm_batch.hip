@@ -53,8 +53,9 @@ struct BatchPlan {
     int packing = 1;
     bool chain = false;      // segment chains first (default tuning knobs, FP32)
     // device memory and the pinned host copy of the descriptor tables at its
-    // start (sets and prep jobs first): they grow and are kept from plan to
-    // plan.  `copied` follows the last copy out of the pinned buffer.
+    // start (sets and prep jobs first).  Another plan takes both over, once the
+    // device has been synchronised; events, streams and graphs are a plan's own.
+    // `copied` follows the last copy out of the pinned buffer.
     void *mem = nullptr;
     size_t mem_bytes = 0;
     char *host = nullptr;
@@ -76,8 +77,7 @@ struct BatchPlan {
     // captured launch sequence (classes forked onto parallel branches): from
     // the second call with the same descriptors on, the first one launches it
     // directly on the caller's stream (a capture costs more than the launches
-    // it saves once).  The capture's streams and events belong to the plan:
-    // none that a capture has used serves another plan or a direct launch.
+    // it saves once).
     bool launched = false;
     static constexpr int kBranches = 4;
     hipStream_t cap = nullptr;
@@ -226,13 +226,17 @@ const void *serial_kernel(int KP)
     }
 }
 
-// Device memory and pinned table buffer of at least `bytes` (the tables are a
-// part of it).  Work that still reads an old buffer is waited for.
-int ensure_memory(BatchPlan &bp, size_t bytes)
+// Whether a buffer of `held` bytes serves a plan that needs `bytes`: large
+// enough, and not so large that a small plan would hold on to a big one's.
+bool serves(size_t held, size_t bytes) { return held >= bytes && held / 4 <= bytes + (size_t(4) << 20); }
+
+// Device memory of a plan (the tables are a part of it) and their pinned copy:
+// the ones taken over where they serve (nothing is queued that uses them),
+// else new ones.  32 mixed sets with other descriptors on every call: 690 us
+// instead of 1,188 with new ones each time.
+int allocate(BatchPlan &bp, size_t bytes)
 {
-    if (!bp.copied && hipEventCreateWithFlags(&bp.copied, hipEventDisableTiming) != hipSuccess) return HMM_E_DEVICE;
-    if (bytes > bp.mem_bytes) {
-        if (hipDeviceSynchronize() != hipSuccess) return HMM_E_DEVICE;
+    if (!serves(bp.mem_bytes, bytes)) {
         if (bp.mem) (void)hipFree(bp.mem);
         bp.mem = nullptr;
         bp.mem_bytes = 0;
@@ -243,21 +247,18 @@ int ensure_memory(BatchPlan &bp, size_t bytes)
         }
         bp.mem_bytes = bytes;
     }
-    // the last copy out of the pinned buffer is over before it is rewritten
-    if (hipEventSynchronize(bp.copied) != hipSuccess) return HMM_E_DEVICE;
-    if (bp.table_bytes > bp.host_bytes) {
+    if (!serves(bp.host_bytes, bp.table_bytes)) {
         if (bp.host) (void)hipHostFree(bp.host);
         bp.host = nullptr;
         bp.host_bytes = 0;
-        const size_t want = bp.table_bytes + bp.table_bytes / 4;
-        if (hipHostMalloc(reinterpret_cast<void **>(&bp.host), want, hipHostMallocDefault) != hipSuccess) {
+        if (hipHostMalloc(reinterpret_cast<void **>(&bp.host), bp.table_bytes, hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
             bp.host = nullptr;
             return HMM_E_NOMEM;
         }
-        bp.host_bytes = want;
+        bp.host_bytes = bp.table_bytes;
     }
-    return HMM_OK;
+    return hipEventCreateWithFlags(&bp.copied, hipEventDisableTiming) == hipSuccess ? HMM_OK : HMM_E_DEVICE;
 }
 
 // Copies the first `bytes` of the tables, ordered on st after the launches
@@ -497,7 +498,7 @@ int build(hmm_ctx *ctx, BatchPlan &bp, hipStream_t st)
         o_e[ci] = take(sizeof(long long) * KP * np);
         o_s[ci] = take(sizeof(long long) * np);
     }
-    int rc = ensure_memory(bp, off);
+    int rc = allocate(bp, off);
     if (rc != HMM_OK) return rc;
     char *base = static_cast<char *>(bp.mem);
     bp.sets = reinterpret_cast<SetDesc *>(base + o_sets);
@@ -737,20 +738,16 @@ int get_plan(hmm_ctx *ctx, int n, const int32_t *K, const int64_t *T, const int6
         return capturing(st) ? HMM_E_DEVICE : set_pointers(*old, params, flag, xy, out, st);
     }
     if (capturing(st)) return HMM_E_DEVICE;
+    // launches, copies and graph replays of the old plan are over before
+    // anything it owns is given back or taken over
+    if (old && hipDeviceSynchronize() != hipSuccess) return HMM_E_DEVICE;
     BatchPlan *bp = new (std::nothrow) BatchPlan;
     if (!bp) return HMM_E_NOMEM;
     if (old) {
-        // a graph may still be running; direct launches are ordered before
-        // the new tables by the stream
-        if (old->exec && hipDeviceSynchronize() != hipSuccess) {
-            delete bp;
-            return HMM_E_DEVICE;
-        }
         std::swap(bp->mem, old->mem);
         std::swap(bp->mem_bytes, old->mem_bytes);
         std::swap(bp->host, old->host);
         std::swap(bp->host_bytes, old->host_bytes);
-        std::swap(bp->copied, old->copied);
         batch_plan_free(old);
         ctx->batch = nullptr;
     }
@@ -771,7 +768,7 @@ int get_plan(hmm_ctx *ctx, int n, const int32_t *K, const int64_t *T, const int6
     bp->chain = algo == HMM_BLOCKED_F32 && ctx->default_plan();
     const int rc = build(ctx, *bp, st);
     if (rc != HMM_OK) {
-        (void)hipDeviceSynchronize();   // an earlier call may still use the buffers
+        (void)hipDeviceSynchronize();   // a copy of the tables may be on its way
         batch_plan_free(bp);
         return rc;
     }
@@ -898,7 +895,7 @@ int hmm_autotune_batched(hmm_ctx *ctx, int32_t n, const int32_t *K, const int64_
     std::vector<int> ks(K, K + n);
     std::sort(ks.begin(), ks.end());
     ks.erase(std::unique(ks.begin(), ks.end()), ks.end());
-    // the candidates' plans reuse the context's buffers on a stream of their own
+    // the candidates run on a stream of their own
     if (hipDeviceSynchronize() != hipSuccess) return HMM_E_DEVICE;
     hipStream_t st = nullptr;
     if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess) return HMM_E_DEVICE;
