@@ -265,32 +265,35 @@ int allocate(BatchPlan &bp, size_t bytes)
 // that still read the old ones.
 int upload(BatchPlan &bp, size_t bytes, hipStream_t st)
 {
-    if (hipMemcpyAsync(bp.mem, bp.host, bytes, hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipEventRecord(bp.copied, st) != hipSuccess) {
-        (void)hipGetLastError();
-        return HMM_E_DEVICE;
-    }
-    return HMM_OK;
+    const bool sent = hipMemcpyAsync(bp.mem, bp.host, bytes, hipMemcpyHostToDevice, st) == hipSuccess;
+    if (sent && hipEventRecord(bp.copied, st) == hipSuccess) return HMM_OK;
+    (void)hipGetLastError();
+    if (sent) (void)hipStreamSynchronize(st);   // no event says when the copy is over
+    return HMM_E_DEVICE;
 }
 
 // New input and output buffers for a plan's descriptors: only the pointers in
-// the tables change.
+// the tables change.  The plan has no buffers (no call matches it) until the
+// copy is under way, so a call after a failed one copies again.
 int set_pointers(BatchPlan &bp, const double *params, const uint8_t *flag, const double *xy, double *out,
                  hipStream_t st)
 {
     if (hipEventSynchronize(bp.copied) != hipSuccess) return HMM_E_DEVICE;
     SetDesc *hs = reinterpret_cast<SetDesc *>(bp.host);
     PrepJob *hp = reinterpret_cast<PrepJob *>(bp.host + bp.o_prep);
-    bp.params = params;
-    bp.flag = flag;
-    bp.xy = xy;
-    bp.out = out;
+    bp.out = nullptr;
     for (int s = 0; s < bp.n; ++s) {
         hs[s].obs = Obs{flag + bp.obs_off[s], xy + 2 * bp.obs_off[s], nullptr, kEmisTremor, 0};
         hs[s].delta = hp[s].params = params + bp.param_off[s];
         hs[s].out = out + s;
     }
-    return upload(bp, bp.pointer_bytes, st);
+    const int rc = upload(bp, bp.pointer_bytes, st);
+    if (rc != HMM_OK) return rc;
+    bp.params = params;
+    bp.flag = flag;
+    bp.xy = xy;
+    bp.out = out;
+    return HMM_OK;
 }
 
 // Workgroups of a kernel that a CU holds at once (asked once per launch shape).
@@ -798,6 +801,25 @@ int check_batch(hmm_ctx *ctx, int32_t n, const int32_t *K, const int64_t *T, con
     return HMM_OK;
 }
 
+int run_batch(hmm_ctx *ctx, int n, const int32_t *K, const int64_t *T, const int64_t *param_off,
+              const double *params, const int64_t *obs_off, const uint8_t *flag, const double *xy, int algo,
+              double *out, hipStream_t st)
+{
+    BatchPlan *bp = nullptr;
+    int rc = get_plan(ctx, n, K, T, param_off, params, obs_off, flag, xy, algo, out, st, &bp);
+    if (rc != HMM_OK) return rc;
+    const bool user_capture = capturing(st);
+    if (ctx->batch_graph && bp->launched && !bp->exec && !user_capture) {
+        rc = capture(*bp);
+        if (rc != HMM_OK) return rc;
+    }
+    if (bp->exec && !user_capture) return hipGraphLaunch(bp->exec, st) == hipSuccess ? HMM_OK : HMM_E_DEVICE;
+    rc = enqueue(*bp, st);
+    if (rc != HMM_OK) return rc;
+    bp->launched = true;
+    return hipGetLastError() == hipSuccess ? HMM_OK : HMM_E_DEVICE;
+}
+
 }  // namespace
 
 }  // namespace hmmh
@@ -815,25 +837,9 @@ int hmm_loglik_batched(hmm_ctx *ctx, int32_t n, const int32_t *K, const int64_t 
     DeviceGuard dg(ctx->device);
     if (!dg.ok) return HMM_E_DEVICE;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    BatchPlan *bp = nullptr;
-    rc = get_plan(ctx, n, K, T, param_off, params, obs_off, flag, xy, algo, out, st, &bp);
-    if (rc != HMM_OK) return rc;
-    const bool user_capture = capturing(st);
-    if (ctx->batch_graph && bp->launched && !bp->exec && !user_capture) {
-        rc = capture(*bp);
-        if (rc != HMM_OK) return rc;
-    }
-    if (bp->exec && !user_capture) {
-        if (hipGraphLaunch(bp->exec, st) != hipSuccess) {
-            (void)hipGetLastError();
-            return HMM_E_DEVICE;
-        }
-        return HMM_OK;
-    }
-    rc = enqueue(*bp, st);
-    if (rc != HMM_OK) return rc;
-    bp->launched = true;
-    return hipGetLastError() == hipSuccess ? HMM_OK : HMM_E_DEVICE;
+    rc = run_batch(ctx, n, K, T, param_off, params, obs_off, flag, xy, algo, out, st);
+    if (rc != HMM_OK) (void)hipGetLastError();   // reported here, not by the next call
+    return rc;
 }
 
 int hmm_ctx_set_batch_graph(hmm_ctx *ctx, int32_t on)

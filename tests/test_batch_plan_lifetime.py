@@ -117,7 +117,47 @@ def many_changes(L):
         L.clean()
 
 
-CASES = {f.__name__: f for f in (descriptors_change, many_changes)}
+def failed_copy(L):
+    """A call whose copy of the new pointers failed leaves no plan that matches
+    them: the next call copies again instead of using the old buffers."""
+    a = sets(np.random.default_rng(2), 5, 20, 40, 2000, 9000)
+    for uses in (1, 3):
+        for at in (1, 2, 3):   # waiting for the last copy, the copy, the event after it
+            for _ in range(uses):
+                assert L.call(a) == 0
+            b = others(a)
+            L.m.model_fail_at(at)
+            assert L.call(b) == -3
+            L.m.model_fail_at(0)
+            before = L.count("copies")
+            assert L.call(b) == 0
+            assert L.count("copies") == before + 1, (uses, at)
+            assert L.call(b) == 0 and L.count("copies") == before + 1
+            L.clean()
+
+
+def any_call_fails(L):
+    """Each runtime call in turn fails: an error comes back, nothing is misused,
+    and the call after it works."""
+    rng = np.random.default_rng(3)
+    a, b = (sets(rng, 6, 4, 73, 2000, 9000) for _ in range(2))
+    c = others(b)
+    for seq in ((a, b, b, c), (c, a, a, a)):
+        for d in seq:   # kernels' attributes are set once
+            assert L.call(d) == 0
+        for at in range(1, 400):
+            start = L.count("calls")
+            L.m.model_fail_at(at)
+            codes = [L.call(d) for d in seq]
+            L.m.model_fail_at(0)
+            L.clean()
+            assert all(L.call(d) == 0 for d in seq), at
+            if L.count("calls") - start < at or not any(codes):
+                break
+        assert at > 20
+
+
+CASES = {f.__name__: f for f in (descriptors_change, many_changes, failed_copy, any_call_fails)}
 
 
 @pytest.fixture(scope="module")
