@@ -23,6 +23,9 @@ const void *pick(int nsl)
 
 }  // namespace
 
-const void *chain_kernel_kinds(int nsl, bool big) { return big ? pick<true, 1>(nsl) : pick<false, 1>(nsl); }
+// up to 16 states every sequence the chains serve takes the larger shape
+static_assert(chain_min_T(16) >= chain_big_T(16) && chain_min_T(4) >= chain_big_T(4));
+
+const void *chain_kernel_kinds(int nsl, bool big) { return big ? pick<true, 1>(nsl) : pick<false, 5>(nsl); }
 
 }  // namespace hmmh

@@ -211,7 +211,7 @@ inline Plan make_plan(const hmm_ctx *ctx, int KP, int64_t T, int packG, int pack
 // 32-bit offsets.
 constexpr int64_t kChainMinLen = 32, kChainMaxLen = int64_t(1) << 22;
 // From this many observations on the larger workgroup shape is used.
-inline int64_t chain_big_T(int K) { return K <= 32 ? 400000 : 1250000; }
+constexpr int64_t chain_big_T(int K) { return K <= 32 ? 400000 : 1250000; }
 
 // Shortest sequence the segment chains are tried on.  They replace K^3 by K^2
 // work but cost two launches more (about 5 us each) and a warm-up of 40..112
@@ -222,7 +222,7 @@ inline int64_t chain_big_T(int K) { return K <= 32 ? 400000 : 1250000; }
 //   K = 33  T = 200 148 / 60,  1e6 1490 / 125   K = 80  T = 200 344 / 140, 1e6 8170 / 300
 // Few states also mix slowly as a rule, and a chain that is given back has
 // cost its attempt, so up to 16 states the line lies where that is small.
-inline int64_t chain_min_T(int K)
+constexpr int64_t chain_min_T(int K)
 {
     return K <= 4 ? 4000000 : (K <= 16 ? 1000000 : (K <= 25 ? 1000 : 64));
 }
