@@ -139,46 +139,58 @@ using uniform_ptr = const __attribute__((address_space(4))) T *;
 
 // The observations of one pair's segments, addressed by 32-bit offsets from a
 // wave-uniform base (the first observation its warm-up can reach): scalar base
-// and one vector register per address.  Offsets are clamped to the record, so
-// every load is unconditional and can stay in flight across chunks; T >= 4.
+// and one vector register per address.  Every load is unconditional and can
+// stay in flight across chunks; flags, counts and values are clamped to the
+// record (T >= 4).  Locations belong to the caller only where the flag is 1:
+// they come through a buffer descriptor, and an observation without one asks
+// for an offset outside it, which reads as zero and touches no memory.
 struct RawObs {
     double x, y;
     int f;
 };
 
+// Most observations a window reaches over: a pair's segments (kChainCols of at
+// most 2^22 observations), its warm-up and the chunks fetched ahead.
+constexpr int kChainWindow = 1 << 27;
+
 template <bool GEN>
 struct ObsWindow {
-    global_ptr<const char> flag, xy;   // flag / cnt and xy / values at the base
+    global_ptr<const char> flag, xy;   // flag / cnt and values at the base
+    __amdgpu_buffer_rsrc_t loc;        // locations from the base on
     int kind;
     int hi;                            // last observation of the record, relative to the base
 
     __device__ __forceinline__ void init(const Obs &o, int64_t base, int64_t T)
     {
         kind = GEN ? o.kind : kEmisTremor;
+        hi = scalar((int)min((int64_t)kChainWindow - 1, T - 1 - base));
         const char *f = nullptr, *v = nullptr;
         if (kind == kEmisPoisson) f = reinterpret_cast<const char *>(o.cnt + base);
         else if (kind == kEmisTremor) f = reinterpret_cast<const char *>(o.flag + base);
-        if (kind == kEmisTremor) v = reinterpret_cast<const char *>(o.xy + 2 * base);
-        else if (kind == kEmisGauss1) v = reinterpret_cast<const char *>(o.xy + base);
+        if (GEN && kind == kEmisGauss1) v = reinterpret_cast<const char *>(o.xy + base);
         flag = (global_ptr<const char>)f;
         xy = (global_ptr<const char>)v;
-        hi = scalar((int)min((int64_t)0x3fffffff, T - 1 - base));
+        if constexpr (!GEN)
+            loc = __builtin_amdgcn_make_buffer_rsrc(const_cast<double *>(o.xy + 2 * base), 0, (int)(16u * (hi + 1u)),
+                                                    0x00020000);
     }
-    // The location (or value) of observation o, the location whatever the
-    // flag says (it is ignored unless the flag is 1); a count goes to f.
-    __device__ __forceinline__ RawObs value(int o) const
+    // Observation o: tremor model, the location where its flag is 1; other
+    // kinds, the count (to f) or the value.
+    __device__ __forceinline__ RawObs value(int o, int f) const
     {
         RawObs r{0.0, 0.0, 1};
-        const uint32_t i = (uint32_t)min(max(o, 0), hi);
-        if (kind == kEmisTremor) {
-            typedef double pair_t __attribute__((ext_vector_type(2)));
-            const pair_t p = *(global_ptr<const pair_t>)(xy + 16u * i);
-            r.x = p.x;
-            r.y = p.y;
-        } else if (kind == kEmisPoisson) {
-            r.f = *(global_ptr<const int32_t>)(flag + 4u * i);
+        if constexpr (!GEN) {
+            // outside the record (o < 0, o > hi) the offset is outside the descriptor too
+            const uint32_t at = f == 1 ? 16u * (uint32_t)o : 0xfffffff0u;
+            typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+            const u4 p = __builtin_amdgcn_raw_buffer_load_b128(loc, (int)at, 0, 0);
+            r.x = __hiloint2double((int)p.y, (int)p.x);
+            r.y = __hiloint2double((int)p.w, (int)p.z);
         } else {
-            r.x = *(global_ptr<const double>)(xy + 8u * i);
+            (void)f;
+            const uint32_t i = (uint32_t)min(max(o, 0), hi);
+            if (kind == kEmisPoisson) r.f = *(global_ptr<const int32_t>)(flag + 4u * i);
+            else r.x = *(global_ptr<const double>)(xy + 8u * i);
         }
         return r;
     }
@@ -187,8 +199,8 @@ struct ObsWindow {
     __device__ __forceinline__ int flag_word(int o) const
     {
         typedef int word_t __attribute__((aligned(1)));
-        if (kind != kEmisTremor) return 0;
-        return *(global_ptr<const word_t>)(flag + (uint32_t)min(max(o, 0), hi - 3));
+        if constexpr (GEN) return 0;
+        else return *(global_ptr<const word_t>)(flag + (uint32_t)min(max(o, 0), hi - 3));
     }
     // flag of observation o + u, from that word
     __device__ __forceinline__ int flag_of(int word, int o, int u) const
@@ -237,8 +249,7 @@ __device__ __forceinline__ double chain_log2_emission(const double (&c)[8], int 
 }
 
 // Validity of one observation; an invalid one is replaced by "no tremor" (its
-// result is discarded).  mask: all ones where the density branch applies; the
-// other branch ignores the location bit by bit, whatever it holds.
+// result is discarded).  mask: all ones where the density branch applies.
 template <bool GEN>
 __device__ __forceinline__ void chain_check_obs(int kind, bool live, RawObs &o, int &mask, int &bad)
 {
@@ -310,7 +321,8 @@ struct ChainStager<NSL, GEN, NS, true> {
     long long ssum;          // shifts of the segment (the same on the four lanes of a segment)
     double cst[NSL][8];
     RawObs raw[D][NU];
-    int words[D];
+    int words[D];            // their flags
+    int ahead[D];            // the flags of the D chunks after those
 
     __device__ __forceinline__ void init(const SetDesc &d, int64_t b0, int64_t base, int W, int lane, int part)
     {
@@ -326,17 +338,22 @@ struct ChainStager<NSL, GEN, NS, true> {
 #pragma unroll
             for (int f = 0; f < 8; ++f) cst[j][f] = sc[8 * (4 * j + g) + f];
     }
+    // (ahead[slot] holds the chunk's flags)
     __device__ __forceinline__ void fetch(int rel, int slot)
     {
-        words[slot] = win.flag_word(off + rel);
+        words[slot] = ahead[slot];
+        ahead[slot] = win.flag_word(off + rel + D * kChainStep);
 #pragma unroll
-        for (int u = 0; u < NU; ++u) raw[slot][u] = win.value(off + rel + u0 + u);
+        for (int u = 0; u < NU; ++u)
+            raw[slot][u] = win.value(off + rel + u0 + u, win.flag_of(words[slot], off + rel, u0 + u));
     }
     __device__ __forceinline__ bool counts() const { return g == 0; }
     // the first chunk of a pass starts at step rel
     __device__ __forceinline__ void start(int rel)
     {
         ssum = 0;
+#pragma unroll
+        for (int k = 0; k < D; ++k) ahead[k] = win.flag_word(off + rel + k * kChainStep);
 #pragma unroll
         for (int k = 0; k < D; ++k) fetch(rel + k * kChainStep, k);
     }
@@ -399,7 +416,7 @@ struct ChainStager<NSL, GEN, 1, false> {
     long long ssum;
     uniform_ptr<d8> sc;
     RawObs raw[D];
-    int words[D];
+    int words[D], ahead[D];
 
     __device__ __forceinline__ void init(const SetDesc &d, int64_t b0, int64_t base, int W, int lane_, int)
     {
@@ -413,13 +430,16 @@ struct ChainStager<NSL, GEN, 1, false> {
     }
     __device__ __forceinline__ void fetch(int rel, int slot)
     {
-        words[slot] = win.flag_word(off + rel);
-        raw[slot] = win.value(off + rel);
+        words[slot] = ahead[slot];
+        ahead[slot] = win.flag_word(off + rel + D * kChainStep);
+        raw[slot] = win.value(off + rel, win.flag_of(words[slot], off + rel, 0));
     }
     __device__ __forceinline__ bool counts() const { return true; }
     __device__ __forceinline__ void start(int rel)
     {
         ssum = 0;
+#pragma unroll
+        for (int k = 0; k < D; ++k) ahead[k] = win.flag_word(off + rel + k * kChainStep);
 #pragma unroll
         for (int k = 0; k < D; ++k) fetch(rel + k * kChainStep, k);
     }

@@ -572,14 +572,18 @@ __global__ __launch_bounds__(64 * post_waves<KB>()) void k_post_forward(PostDesc
     for (int i = 0; i < KK; ++i) gcol[i] = gs[i * KB + jc];
     if (j < KB) su[j] = live ? (float)d.Aseg[b * K + j] : 0.f;
     wsync();
-    // lane (h, j): observation j of the chunk of segment h, the next chunk's in flight
+    // lane (h, j): observation j of the chunk of segment h, the next chunk's in
+    // flight and its flag a chunk earlier: where that is not 1 the location is
+    // not the caller's to read (a word of the constants instead, never used)
     const int64_t tf = b < d.nb ? t0 : 0;
-    uint8_t flag;
+    auto place = [&](int rc) { return min(tf + rc + j, d.T - 1); };
+    uint8_t flag, ahead = d.flag[place(0)];
     double2 xy;
     auto fetch = [&](int rc) {
-        const int64_t t = min(tf + rc + j, d.T - 1);
-        flag = d.flag[t];
-        xy = reinterpret_cast<const double2 *>(d.xy)[t];
+        flag = ahead;
+        xy = *(flag == 1 ? reinterpret_cast<const double2 *>(d.xy) + place(rc)
+                         : reinterpret_cast<const double2 *>(d.sc));
+        ahead = d.flag[place(rc + HW)];
     };
     fetch(0);
     for (int rc = 0; rc < longest; rc += HW) {

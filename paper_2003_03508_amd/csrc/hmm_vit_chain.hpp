@@ -248,16 +248,22 @@ __global__ __launch_bounds__(64) void k_vit_chain(VitChain v, int mode)
         for (int s = 0; s < NS; ++s) d[s] = fin ? d[s] - top : d[s];
     }
 
-    // observations of the next chunk, one per lane
+    // observations of the next chunk, one per lane; the flag a chunk earlier:
+    // where it is not 1 the location is not the caller's to read (a word of the
+    // constants instead, never used)
     double ox, oy;
-    int of, bad = 0;
+    int of, oflag, bad = 0;
+    auto place = [&](int rel) {
+        const int64_t t = t0 + rel + l;
+        return t < 0 ? (int64_t)0 : (t < v.T ? t : v.T - 1);
+    };
     auto fetch = [&](int rel) {
-        int64_t t = t0 + rel + l;
-        t = t < 0 ? 0 : (t < v.T ? t : v.T - 1);
-        const double2 p = reinterpret_cast<const double2 *>(v.xy)[t];
+        of = oflag;
+        const double2 p = *(of == 1 ? reinterpret_cast<const double2 *>(v.xy) + place(rel)
+                                    : reinterpret_cast<const double2 *>(v.sc));
         ox = p.x;
         oy = p.y;
-        of = v.flag[t];
+        oflag = v.flag[place(rel + HW)];
     };
     // steps that the segment takes: inside the record, to its lookahead's end
     const int ahead = mode == 1 || flat ? 0 : kVitAhead;   // a rerun knows its end state
@@ -277,6 +283,7 @@ __global__ __launch_bounds__(64) void k_vit_chain(VitChain v, int mode)
     auto walk = [&](int from, int to, auto kind_) {
         constexpr int KIND = decltype(kind_)::value;
         constexpr bool MAIN = KIND == 1;
+        oflag = v.flag[place(from)];
         fetch(from);
         for (int rc = from; rc < to; rc += HW) {
             {   // the chunk's observations to LDS, the next chunk's loads in flight
@@ -431,9 +438,11 @@ __global__ __launch_bounds__(256) void k_vit_path_score(VitChain v)
         if (lane < n) {
             const int64_t t = tc + lane;
             const int j = v.path[t], i = t > 0 ? v.path[t - 1] : v.pre[0];
-            const double2 x = reinterpret_cast<const double2 *>(v.xy)[t];
+            const bool tremor = v.flag[t] == 1;
+            double2 x{0.0, 0.0};
+            if (tremor) x = reinterpret_cast<const double2 *>(v.xy)[t];
             a = v.lg[i * v.KB + j];
-            e = (float)state_log2_emission(v.sc[j], v.flag[t] == 1, x.x, x.y);
+            e = (float)state_log2_emission(v.sc[j], tremor, x.x, x.y);
             m = v.mx[t];
         }
         acc += (double)m;
