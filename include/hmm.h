@@ -93,12 +93,16 @@ typedef enum {
      * vectors, O(T K^2) work: each segment starts from a flat vector 40..112
      * observations early, and on the device every segment's start is checked,
      * entry by entry (relative 2^-16), against the end of the segment before
-     * it; segments that differ are run again from there.  Where the check is
-     * not met (chains that hardly forget), and where Gamma has an entry below
-     * 2^-56 (zeros included), the products above are computed in the same
-     * call.  Both give ln L within the same FP32 rounding.  Used for K > 25
-     * from T = 64, K > 16 from T = 1000, smaller K from T = 10^6 (K > 4) or 4 10^6, where
-     * it is the faster one. */
+     * it; segments that differ are run again from there, and so are segments
+     * whose differences add up to more than 2^-24 per observation and per nat
+     * of ln L.  Where the check is not met (chains that hardly forget), and
+     * where Gamma has an entry below 2^-56 (zeros included), the products above
+     * are computed in the same call.  Both give ln L within FP32 rounding:
+     * about 1e-9 |ln L| in records with events; where the same observation
+     * recurs (a record without events) its rounding recurs too, and either is
+     * off by up to 2e-7 nats per observation.  Used for K > 25 from T = 64,
+     * K > 16 from T = 1000, smaller K from T = 10^6 (K > 4) or 4 10^6, where it
+     * is the faster one. */
     HMM_BLOCKED_F32 = 1,
     /* The same plan with the segment products on 16-bit MFMA: the running
      * product and the emission-scaled transition matrix are rounded to bf16

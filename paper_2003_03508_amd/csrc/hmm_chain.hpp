@@ -8,12 +8,20 @@
 // `warm` steps before its first observation, holds s_b (its start vector) when
 // it gets there and e_b (its end vector) after its last one, and
 //     ln L = ln sum(delta) + sum_b ln( sum(e_b) / sum(s_b) )
-// provided that s_b is parallel to e_{b-1}.  That is checked for every
-// segment, entry by entry (relative difference <= kChainTol, i.e. the
-// projective distance of the two vectors, which the remaining chain cannot
-// increase); a segment that starts elsewhere is run again from e_{b-1}.  Where
-// the check cannot be met the set's `fail` word is raised and the launches of
-// the product path behind it, which otherwise return at once, compute ln L.
+// provided that s_b is parallel to e_{b-1}.  That is checked for every segment,
+// entry by entry (relative difference eps_b <= kChainTol, i.e. the projective
+// distance of the two vectors, which the remaining chain cannot increase); a
+// segment that starts elsewhere is run again from e_{b-1}.  Where the check
+// cannot be met the set's `fail` word is raised and the launches of the product
+// path behind it, which otherwise return at once, compute ln L.
+//
+// ln L is off by at most sum_b eps_b.  What is left of a flat start has the
+// same sign in every segment of a record without events, so a walker whose sum
+// is more than rounding may come to (chain_budget) runs its segments once more,
+// from their neighbours' ends: what the flat starts left shrinks by the rate of
+// the first run, what rounding left does not, and stands.  (Two groups of
+// states, K = 20, T = 20,000, no events: ln L off by 1.4e-6 relative without
+// the second run, by 8e-8 with it; 36 -> 45 us.)
 //
 // Work: K^2 instead of K^3 multiply-adds per observation.  A step is a matrix
 // product again: the start-state columns of the product path become the
@@ -29,7 +37,7 @@ constexpr int kChainStep = 4;      // steps per staged chunk: 16 x 4 observation
 constexpr int kChainRepairs = 3;   // reruns of segments from their neighbours' ends
 constexpr float kChainTol = 0x1p-16f;
 // The scale of a column lags one step behind, so a column's largest entry
-// varies; below this a flushed entry could matter (see chain_usable).
+// varies; below this a flushed entry could matter (see kChainMinGamma).
 constexpr float kChainLow = 0x1p-40f;
 
 // Sum over the four lanes that hold one column of a 16-wide tile.
@@ -61,6 +69,25 @@ __device__ __forceinline__ int64_t scalar(int64_t x)
     return (int64_t)(((uint64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32) | lo);
 }
 
+// What a walker's starts may differ by in sum without another run: obs
+// observations, ln: its part of ln L.  FP32 rounds every entry at every
+// observation, and where an observation recurs so does its rounding: ln L of a
+// record without events is off by 0.1..2e-7 per observation (segment products
+// and vectors alike, K = 20..80).
+__device__ __forceinline__ float chain_budget(int64_t obs, double ln)
+{
+    return 0x1p-24f * ((float)obs + fabsf((float)ln));
+}
+
+// Relative difference of an entry s from its neighbour's r e; what lies below
+// 2^-100 of the sum ss is not compared (it cannot contribute: a vector whose
+// entries spread that far is refused, kChainLow and kChainMinGamma).
+__device__ __forceinline__ float chain_diff(float s, float e, float ss, float r)
+{
+    const float d = fabsf(s - r * e) - 0x1p-100f * ss;
+    return d > 0.f ? d / fmaxf(s, r * e) : 0.f;
+}
+
 // Whether reruns can still meet the tolerance.  The largest relative difference
 // diff is left after `steps` steps of forgetting; at that rate the tolerance
 // needs steps * ln(tol) / ln(diff) of them, and `left` more are available
@@ -72,8 +99,7 @@ __device__ __forceinline__ bool chain_hopeless(float diff, int steps, int left)
 }
 
 // s parallel to e: |s - r e| <= tol s with r = ss / es (ss, es the sums of
-// the two vectors); entries below 2^-100 of the sum are not compared (they
-// cannot contribute, chain_usable).  False for NaN and for a zero vector.
+// the two vectors), with chain_diff's limit.  False for NaN and for a zero vector.
 __device__ __forceinline__ bool chain_parallel(float s, float e, float ss, float r)
 {
     return fabsf(s - r * e) <= kChainTol * s + 0x1p-100f * ss;
@@ -508,7 +534,8 @@ __device__ __forceinline__ void chain_body(const SetDesc &d, int64_t wg, int mod
 {
     typedef Tile<16>::acc_t acc_t;
     extern __shared__ __attribute__((aligned(16))) float smem[];
-    int *ism = reinterpret_cast<int *>(smem);
+    int *ism = reinterpret_cast<int *>(smem);                           // a verdict per walker
+    long long *shifts = reinterpret_cast<long long *>(smem) + 8;        // a sum per stager
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const bool walker = wave < NP;
@@ -584,15 +611,17 @@ __device__ __forceinline__ void chain_body(const SetDesc &d, int64_t wg, int mod
                     chain_barrier();
                 }
             }
-            chain_barrier();   // the walkers' verdicts are in LDS
+            // the buffers are free: the shifts of the pass for the walker's
+            // part of ln L, then its verdict
+            const long long ssum = wave_sum_i64(sg.counts() ? sg.ssum : 0);
+            if (lane == 0) shifts[pair * NS + share] = ssum;
+            chain_barrier();
+            chain_barrier();
             const int any = verdicts();
             chain_barrier();
             if (any != 1 || pass == kChainRepairs) break;
         }
         if (__any(sg.bad) && lane == 0) atomicOr(d.status, kBadData);
-        const long long ssum = wave_sum_i64(sg.counts() ? sg.ssum : 0);
-        if (lane == 0) reinterpret_cast<long long *>(smem)[8 + pair * NS + share] = ssum;
-        chain_barrier();
         return;
     }
 
@@ -700,6 +729,8 @@ __device__ __forceinline__ void chain_body(const SetDesc &d, int64_t wg, int mod
     };
 
     float ss = 0.f, es = 0.f;
+    double part = 0.0;
+    bool settled = false;   // another run for the sum of the differences has been asked for
     for (int pass = 0;; ++pass) {
         const int rel0 = pass == 0 ? -W : 0;
         int o = 0;   // buffer of the chunk
@@ -726,25 +757,42 @@ __device__ __forceinline__ void chain_body(const SetDesc &d, int64_t wg, int mod
         es = column_total(y);
         const float pes = from_left_column(es);
         const float r = ss / pes;
+        const bool inner = live && c > 0;
         bool ok = true;
-        float pv[NSL];
+        float pv[NSL], diff = 0.f;
 #pragma unroll
         for (int j = 0; j < NSL; ++j) {
             pv[j] = from_left_column(y[j]);
             ok = ok && chain_parallel(s[j], pv[j], ss, r);
+            diff = fmaxf(diff, chain_diff(s[j], pv[j], ss, r));
         }
-        mism = __any(live && c > 0 && !ok);
+        // largest difference of each segment's start, their sum and largest
+        if (!inner) diff = 0.f;
+        diff = fmaxf(diff, __shfl_xor(diff, 32));
+        diff = fmaxf(diff, __shfl_xor(diff, 16));
+        float sum = diff;
+        for (int o2 = 8; o2 > 0; o2 >>= 1) {
+            sum += __shfl_xor(sum, o2);
+            diff = fmaxf(diff, __shfl_xor(diff, o2));
+        }
+        // this walker's part of ln L
+        part = 0.0;
+        if (live && g == 0) part = kLn2 * (double)E + log((double)es / (double)ss);
+        part = wave_sum_f64(part);
+        chain_barrier();   // the stagers' shifts are in LDS
+        long long stot = 0;
+#pragma unroll
+        for (int k = 0; k < NS; ++k) stot += shifts[pair * NS + k];
+        part += kLn2 * (double)stot;
+        const bool sound = fabs(part) < __builtin_inf();   // not L = 0, nothing overflowed
+        mism = __any(inner && !ok) || !sound;
         int verdict = 0;   // bit 0: run again; bit 1: give the set back
         if (mism) {
-            float diff = 0.f;
-#pragma unroll
-            for (int j = 0; j < NSL; ++j) {
-                const float e = fabsf(s[j] - r * pv[j]);
-                if (e > 0x1p-100f * ss) diff = fmaxf(diff, e / fmaxf(s[j], r * pv[j]));
-            }
-            if (!(live && c > 0)) diff = 0.f;
-            for (int o2 = 32; o2 > 0; o2 >>= 1) diff = fmaxf(diff, __shfl_xor(diff, o2));
-            verdict = chain_hopeless(diff, W + pass * rel_end, (kChainRepairs - pass) * rel_end) ? 3 : 1;
+            const bool end = !sound || chain_hopeless(diff, W + pass * rel_end, (kChainRepairs - pass) * rel_end);
+            verdict = end ? 3 : 1;
+        } else if (!settled && sum > chain_budget((int64_t)(last + 1) * q, part)) {
+            verdict = 1;
+            settled = true;
         }
         if (lane == 0) ism[pair] = verdict;
         chain_barrier();
@@ -761,17 +809,7 @@ __device__ __forceinline__ void chain_body(const SetDesc &d, int64_t wg, int mod
         ep = 0;
     }
     bool fail = mism || __any(live && !(mlow >= kChainLow && ss > 0.f && es > 0.f && es < 0x1p+100f));
-    double part = 0.0;
-    if (live && g == 0 && !fail) {
-        double td = (double)es / (double)ss;
-        part = kLn2 * (double)E + log(td);
-    }
-    part = wave_sum_f64(part);
-    chain_barrier();   // the stagers' shift sums are in LDS
     if (!pair_live) return;
-    long long stot = 0;
-#pragma unroll
-    for (int k = 0; k < NS; ++k) stot += reinterpret_cast<const long long *>(smem)[8 + pair * NS + k];
     const global_ptr<float> vep = (global_ptr<float>)(d.ve + gw * KP);
     if (mode == 0) {
         if (c == 0) {
@@ -796,7 +834,7 @@ __device__ __forceinline__ void chain_body(const SetDesc &d, int64_t wg, int mod
         fail = fail || __any(c == last && !ok);
     }
     if (lane == 0) {
-        d.part[gw] = part + kLn2 * (double)stot;
+        d.part[gw] = part;
         if (fail) atomicOr(d.fail, 1);
     }
 }
