@@ -90,12 +90,24 @@ __device__ __forceinline__ float chain_diff(float s, float e, float ss, float r)
 
 // Whether reruns can still meet the tolerance.  The largest relative difference
 // diff is left after `steps` steps of forgetting; at that rate the tolerance
-// needs steps * ln(tol) / ln(diff) of them, and `left` more are available
-// (half as many again are granted, the rate being an estimate).
-__device__ __forceinline__ bool chain_hopeless(float diff, int steps, int left)
+// needs steps * ln(tol) / ln(diff) of them, and `left` more are available,
+// times `grant` (the rate is an estimate).
+__device__ __forceinline__ bool chain_hopeless(float diff, int steps, int left, float grant)
 {
     if (!(diff < 1.f)) return true;
-    return (float)steps * logf(kChainTol) < 1.5f * (float)(steps + left) * logf(fmaxf(diff, kChainTol));
+    return (float)steps * logf(kChainTol) < grant * (float)(steps + left) * logf(fmaxf(diff, kChainTol));
+}
+
+// Reruns of a walker most of whose starts differ: the chain forgets slowly
+// everywhere, so the starts checked across walkers differ too and the second
+// launch walks everything again.  After the first pass n reruns cost
+// W + (2 n + 1) q steps, the segment products behind some 8 q (K = 20, T =
+// 20,000..200,000, q = 32..49: 8 to 10 q; K = 25, T = 10^6, q = 122: 10 q; K =
+// 40: 11 q; K = 80, q = 32: 7 q).
+__device__ __forceinline__ int chain_slow_repairs(int W, int q)
+{
+    const int n = (7 * q - W) / (2 * q);
+    return n < 0 ? 0 : (n < kChainRepairs ? n : kChainRepairs);
 }
 
 // s parallel to e: |s - r e| <= tol s with r = ss / es (ss, es the sums of
@@ -731,6 +743,7 @@ __device__ __forceinline__ void chain_body(const SetDesc &d, int64_t wg, int mod
     float ss = 0.f, es = 0.f;
     double part = 0.0;
     bool settled = false;   // another run for the sum of the differences has been asked for
+    float before = 0.f;     // that sum in the pass before
     for (int pass = 0;; ++pass) {
         const int rel0 = pass == 0 ? -W : 0;
         int o = 0;   // buffer of the chunk
@@ -770,6 +783,7 @@ __device__ __forceinline__ void chain_body(const SetDesc &d, int64_t wg, int mod
         if (!inner) diff = 0.f;
         diff = fmaxf(diff, __shfl_xor(diff, 32));
         diff = fmaxf(diff, __shfl_xor(diff, 16));
+        const int differ = __popcll(__ballot(g == 0 && diff > kChainTol));   // segments
         float sum = diff;
         for (int o2 = 8; o2 > 0; o2 >>= 1) {
             sum += __shfl_xor(sum, o2);
@@ -788,12 +802,16 @@ __device__ __forceinline__ void chain_body(const SetDesc &d, int64_t wg, int mod
         mism = __any(inner && !ok) || !sound;
         int verdict = 0;   // bit 0: run again; bit 1: give the set back
         if (mism) {
-            const bool end = !sound || chain_hopeless(diff, W + pass * rel_end, (kChainRepairs - pass) * rel_end);
+            const bool slow = last >= kChainCols / 2 && 2 * differ > last;
+            const int left = max(0, (slow ? chain_slow_repairs(W, (int)q) : kChainRepairs) - pass);
+            const bool end = !sound || (pass > 0 && sum > 0.5f * before) ||
+                             chain_hopeless(diff, W + pass * rel_end, left * rel_end, slow ? 1.f : 1.5f);
             verdict = end ? 3 : 1;
         } else if (!settled && sum > chain_budget((int64_t)(last + 1) * q, part)) {
             verdict = 1;
             settled = true;
         }
+        before = sum;
         if (lane == 0) ism[pair] = verdict;
         chain_barrier();
         const int any = verdicts();
