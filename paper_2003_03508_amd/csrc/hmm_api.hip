@@ -196,7 +196,7 @@ int loglik_impl(hmm_ctx *ctx, int kind, int32_t K, const double *delta, const do
         StateConst *sc = at<StateConst>(ctx->ws, ly.sc);
         float *gf = at<float>(ctx->ws, ly.gf);
         hipLaunchKernelGGL(k_prepare, dim3(1), dim3(256), 0, st, kind, K, KP, delta, Gamma, a, b, c, sc, gf, status,
-                           (int *)nullptr);
+                           (int *)nullptr, 0.f);
         if (kind == kEmisTremor)
             launch_serial<false>(KP, st, K, T, delta, gf, sc, obs, status, out);
         else
@@ -223,7 +223,7 @@ int loglik_impl(hmm_ctx *ctx, int kind, int32_t K, const double *delta, const do
     StateConst *sc = at<StateConst>(ctx->ws, ly.sc);
     float *gf = at<float>(ctx->ws, ly.gf);
     hipLaunchKernelGGL(k_prepare, dim3(1), dim3(256), 0, st, kind, K, KP, delta, Gamma, a, b, c, sc, gf, status,
-                       cp.nb > 0 ? at<int>(ctx->ws, ly.chain) : nullptr);
+                       cp.nb > 0 ? at<int>(ctx->ws, ly.chain) : nullptr, chain_max_stay(cp.q));
     SetDesc d;
     d.obs = obs;
     d.sc = sc;
@@ -437,12 +437,12 @@ int hmm_loglik_noalloc(int32_t K, const double *delta, const double *Gamma, cons
     if (algo == HMM_SERIAL_F32) {
         const int KP = serial_kp(K);
         hipLaunchKernelGGL(k_prepare, dim3(1), dim3(256), 0, st, kEmisTremor, K, KP, delta, Gamma, p, mu, Sigma,
-                           sc, gf, status, (int *)nullptr);
+                           sc, gf, status, (int *)nullptr, 0.f);
         launch_serial<false>(KP, st, K, T, delta, gf, sc, obs, status, out);
         return launch_status();
     }
     hipLaunchKernelGGL(k_prepare, dim3(1), dim3(256), 0, st, kEmisTremor, K, ks.KP(), delta, Gamma, p, mu, Sigma,
-                       sc, gf, status, cp.nb > 0 ? at<int>(ws, ly.chain) : nullptr);
+                       sc, gf, status, cp.nb > 0 ? at<int>(ws, ly.chain) : nullptr, chain_max_stay(cp.q));
     SetDesc d;
     d.obs = obs;
     d.sc = sc;

@@ -567,6 +567,8 @@ int build(hmm_ctx *ctx, BatchPlan &bp, hipStream_t st)
             set_chain(&d, base, ly, cps[s]);
             pj.chain = d.fail;
         }
+        pj.max_stay = chain_max_stay(cps[s].q);
+        pj.pad = 0;
         pj.K = bp.K[s];
         pj.KP = kp[s];
     }

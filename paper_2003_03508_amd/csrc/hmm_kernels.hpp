@@ -99,7 +99,18 @@ constexpr int kChainWords = 2;
 // K = 8..80 needed 32..96 steps.  What a warm-up misses costs a rerun of the
 // segments, never the result, but one rerun (32..512 steps) costs more than a
 // few steps of warm-up everywhere; past 112 the reruns carry on.
+// Where a second state is left with probability below 1 - stay (one alone, a
+// background state, does not slow the others down) the chains are not tried:
+// they would be given back after their first pass or a few reruns.  stay by the
+// segments' length, measured with informative data (chains tried / not tried /
+// products alone, us; the tried ones were given back unless marked *):
+//   0.95 below 64 observations: second largest 0.955: K = 25, T = 105,000 187 /
+//     131 / 125, K = 40 399 / 291 / 287, K = 64, T = 50,000 672 / 430 / 425, K =
+//     80, T = 400,000 3,847 / 3,394 / 3,393, K = 20, T = 40,000 109* / 105 / 102;
+//     0.9: K = 20, T = 40,000 56* / - / 102, K = 40 107* / - / 286
+//   0.972 above: K = 25, T = 10^6: 0.97 296* / - / 461; 0.975 605 / 464 / 457
 constexpr float kChainMinGamma = 0x1p-56f;
+constexpr float chain_max_stay(int64_t segment) { return segment < 64 ? 0.95f : 0.972f; }
 
 __device__ __forceinline__ int chain_warmup(float dmax)
 {
@@ -108,15 +119,19 @@ __device__ __forceinline__ int chain_warmup(float dmax)
     return (int)fminf(fmaxf(w, 40.f), 112.f);
 }
 
-// Gamma in FP32, zero-padded to KP x KP (pitch KP), its checks, and (chain)
-// its smallest entry and largest diagonal entry in the LDS words red[0] and
-// red[1], which thread 0 sets to {FP32 +inf bits, 0} before a barrier.
+// Gamma in FP32, zero-padded to KP x KP (pitch KP), its checks, and (chain, K <=
+// 80) in the LDS words red[kPrepWords] its smallest entry (red[0], which thread
+// 0 sets to FP32 +inf bits before a barrier) and the largest two diagonal
+// entries of the states 0..63 (red[1], red[2]) and 64..79 (red[3], red[4]).
 // Returns 1 for an invalid entry.
+constexpr int kPrepWords = 5;
+
 __device__ __forceinline__ int prepare_gamma(int K, int KP, const double *__restrict__ Gamma, float *__restrict__ GF,
                                              bool chain, unsigned *red)
 {
     int bad = 0;
-    float gmin = __builtin_inff(), dmax = 0.f;
+    float gmin = __builtin_inff();
+    const float stay = chain && (int)threadIdx.x < K ? (float)Gamma[(int64_t)threadIdx.x * (K + 1)] : 0.f;
     for (int idx = threadIdx.x; idx < KP * KP; idx += blockDim.x) {
         const int i = idx / KP, j = idx % KP;
         float v = 0.f;
@@ -125,29 +140,36 @@ __device__ __forceinline__ int prepare_gamma(int K, int KP, const double *__rest
             if (!(isfinite(gij) && gij >= 0.0 && gij <= 1.0)) bad = 1;
             v = (float)gij;
             gmin = fminf(gmin, v);
-            if (i == j) dmax = fmaxf(dmax, v);
         }
         GF[idx] = v;
     }
     if (!chain) return bad;
     // entries in [0, 1]: bit patterns order like the values (with an invalid
     // one the words are not used); one LDS atomic per wavefront
-    unsigned lo = __float_as_uint(gmin), hi = __float_as_uint(dmax);
+    unsigned lo = __float_as_uint(gmin);
+    float top = stay, second = 0.f;
     for (int o = 32; o > 0; o >>= 1) {
         lo = min(lo, (unsigned)__shfl_xor((int)lo, o));
-        hi = max(hi, (unsigned)__shfl_xor((int)hi, o));
+        const float t = __shfl_xor(top, o), u = __shfl_xor(second, o);
+        second = fmaxf(fminf(top, t), fmaxf(second, u));
+        top = fmaxf(top, t);
     }
     if ((threadIdx.x & 63) == 0) {
         atomicMin(&red[0], lo);
-        atomicMax(&red[1], hi);
+        if (threadIdx.x < 128) {
+            red[1 + threadIdx.x / 32] = __float_as_uint(top);
+            red[2 + threadIdx.x / 32] = __float_as_uint(second);
+        }
     }
     return bad;
 }
 
-__device__ __forceinline__ void write_chain_words(const unsigned *red, int *chain)
+__device__ __forceinline__ void write_chain_words(const unsigned *red, float max_stay, int *chain)
 {
-    chain[0] = __uint_as_float(red[0]) >= kChainMinGamma ? 0 : 1;
-    chain[1] = chain_warmup(__uint_as_float(red[1]));
+    const float a = __uint_as_float(red[1]), b = __uint_as_float(red[3]);
+    const float second = fmaxf(fminf(a, b), fmaxf(__uint_as_float(red[2]), __uint_as_float(red[4])));
+    chain[0] = __uint_as_float(red[0]) >= kChainMinGamma && second < max_stay ? 0 : 1;
+    chain[1] = chain_warmup(fmaxf(a, b));
 }
 
 // kind: kEmisTremor (p, mu, Sigma as in eq. 1) or another kind (p = e0,
@@ -159,14 +181,13 @@ static __global__ __launch_bounds__(256) void k_prepare(int kind, int K, int KP,
                                                  const double *__restrict__ Sigma,
                                                  StateConst *__restrict__ sc,
                                                  float *__restrict__ GF, int *__restrict__ status,
-                                                 int *__restrict__ chain)
+                                                 int *__restrict__ chain, float max_stay)
 {
     __shared__ int bad;
-    __shared__ unsigned red[2];
+    __shared__ unsigned red[kPrepWords];
     if (threadIdx.x == 0) {
         bad = 0;
         red[0] = 0x7f800000u;
-        red[1] = 0u;
     }
     __syncthreads();
     int mybad = 0;
@@ -180,7 +201,7 @@ static __global__ __launch_bounds__(256) void k_prepare(int kind, int K, int KP,
     __syncthreads();
     if (threadIdx.x == 0) {
         *status = bad ? kBadParams : 0;
-        if (chain) write_chain_words(red, chain);
+        if (chain) write_chain_words(red, max_stay, chain);
     }
 }
 
@@ -192,7 +213,8 @@ struct PrepJob {
     float *GF;
     int *status;
     int *chain;   // kChainWords words, or null
-    int K, KP;
+    float max_stay;
+    int K, KP, pad;
 };
 
 static __global__ __launch_bounds__(256) void k_prepare_batch(const PrepJob *__restrict__ jobs)
@@ -202,11 +224,10 @@ static __global__ __launch_bounds__(256) void k_prepare_batch(const PrepJob *__r
     const double *delta = j.params, *Gamma = delta + K, *p = Gamma + (int64_t)K * K, *mu = p + K,
                  *Sigma = mu + 2 * K;
     __shared__ int bad;
-    __shared__ unsigned red[2];
+    __shared__ unsigned red[kPrepWords];
     if (threadIdx.x == 0) {
         bad = 0;
         red[0] = 0x7f800000u;
-        red[1] = 0u;
     }
     __syncthreads();
     int mybad = 0;
@@ -219,7 +240,7 @@ static __global__ __launch_bounds__(256) void k_prepare_batch(const PrepJob *__r
     __syncthreads();
     if (threadIdx.x == 0) {
         *j.status = bad ? kBadParams : 0;
-        if (j.chain) write_chain_words(red, j.chain);
+        if (j.chain) write_chain_words(red, j.max_stay, j.chain);
     }
 }
 

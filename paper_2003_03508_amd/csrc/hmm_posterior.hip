@@ -1303,7 +1303,7 @@ int posterior_impl(hmm_ctx *ctx, int32_t K, const double *delta, const double *G
     StateConst *sc = at<StateConst>(ws, o_sc);
     float *gf = at<float>(ws, o_gf);
     hipLaunchKernelGGL(k_prepare, dim3(1), dim3(256), 0, st, (int)kEmisTremor, K, KP, delta, Gamma, p, mu, Sigma, sc,
-                       gf, status, (int *)nullptr);
+                       gf, status, (int *)nullptr, 0.f);
     SetDesc sd;
     sd.obs = Obs{flag, xy, nullptr, kEmisTremor, 0};
     sd.sc = sc;

@@ -770,11 +770,10 @@ __global__ __launch_bounds__(1024) void k_vit_prepare(int K, int KB, const doubl
                                                       int *__restrict__ status, int *__restrict__ chain)
 {
     __shared__ int bad;
-    __shared__ unsigned red[2];
+    __shared__ unsigned red[kPrepWords];
     if (threadIdx.x == 0) {
         bad = 0;
         red[0] = 0x7f800000u;
-        red[1] = 0u;
     }
     __syncthreads();
     int mybad = 0;
@@ -792,7 +791,7 @@ __global__ __launch_bounds__(1024) void k_vit_prepare(int K, int KB, const doubl
     __syncthreads();
     if (threadIdx.x == 0) {
         *status = bad ? kBadParams : 0;
-        if (chain) write_chain_words(red, chain);
+        if (chain) write_chain_words(red, 2.f, chain);   // whatever its states' stays
     }
 }
 
