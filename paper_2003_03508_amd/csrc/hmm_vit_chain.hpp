@@ -162,6 +162,26 @@ struct VitLds {
 };
 __host__ __device__ constexpr int vit_psi_bytes(int KR, int rows) { return (rows * KR + 128 + 15) / 16 * 16; }
 
+// Whether at least three in four of 64 segments spread over the record start
+// elsewhere than their neighbours end, by eight entries of the vectors: the
+// record forgets too slowly, a rerun of nearly every segment would not meet its
+// old end either.  Asked by wavefronts that have a segment to run again (K = 25,
+// T = 10^6, Gamma_ii 0.95, no location information: 2,020 -> 1,890 us, products
+// alone 1,550; K = 64, T = 105,000: 3,583 -> 3,465, 3,225).
+__device__ __forceinline__ bool vit_most_differ(const VitChain &v, int kr, int lane)
+{
+    if (v.nb <= 64) return false;
+    const int64_t s = 1 + lane * (v.nb - 1) / 64;
+    const float *a = v.sv + s * kr, *e = v.ev + (s - 1) * kr;
+    bool differ = false;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int j = i * v.K / 8;
+        differ = differ || !vit_same(a[j], e[j]);
+    }
+    return __popcll(__ballot(differ)) >= 48;
+}
+
 // mode 0: every segment.  mode 1: the check, and the segments that differ.
 // KK: states the loops run over (K itself for K <= 32).
 template <int KK, int HW>
@@ -204,6 +224,10 @@ __global__ __launch_bounds__(64) void k_vit_chain(VitChain v, int mode)
         }
         redo = seg_max<HW>(bad ? 1.f : 0.f) > 0.f;
         if (!__any(redo)) return;
+        if (vit_most_differ(v, KR, lane)) {
+            if (lane == 0) atomicOr(v.fail, 1);
+            return;
+        }
     }
 
     // constants of this lane's states, and their columns of log2 Gamma
