@@ -245,8 +245,14 @@ inline ChainPlan cut_chain(int64_t T, int64_t L, ChainShape sh)
     return c;
 }
 
+// From 2^39 observations on the walkers' vectors (segments are at most
+// kChainMaxLen) would outgrow the fixed scratch of hmm_loglik_noalloc, which
+// takes any T; the product path alone, with and without a context.
+constexpr int64_t kChainMaxT = int64_t(1) << 39;
+
 inline ChainPlan make_chain_plan(int K, int64_t T)
 {
+    if (T >= kChainMaxT) return ChainPlan();
     const bool big = T >= chain_big_T(K);
     const ChainShape sh = chain_shape(K, big);
     const int64_t segs = 256 * sh.segs();
