@@ -226,14 +226,31 @@ const void *serial_kernel(int KP)
     }
 }
 
+// Ends the context's plan: its launches, copies and graph replays are over
+// before anything it owns is given back or taken over.
+int retire(hmm_ctx *ctx, BatchPlan &bp)
+{
+    BatchPlan *old = ctx->batch;
+    if (!old) return HMM_OK;
+    if (hipDeviceSynchronize() != hipSuccess) return HMM_E_DEVICE;
+    std::swap(bp.mem, old->mem);
+    std::swap(bp.mem_bytes, old->mem_bytes);
+    std::swap(bp.host, old->host);
+    std::swap(bp.host_bytes, old->host_bytes);
+    batch_plan_free(old);
+    ctx->batch = nullptr;
+    return HMM_OK;
+}
+
 // Whether a buffer of `held` bytes serves a plan that needs `bytes`: large
 // enough, and not so large that a small plan would hold on to a big one's.
 bool serves(size_t held, size_t bytes) { return held >= bytes && held / 4 <= bytes + (size_t(4) << 20); }
 
 // Device memory of a plan (the tables are a part of it) and their pinned copy:
 // the ones taken over where they serve (nothing is queued that uses them),
-// else new ones.  32 mixed sets with other descriptors on every call: 690 us
-// instead of 1,188 with new ones each time.
+// else new ones.  32 mixed sets with other descriptors on every call: 533 us;
+// 690 where the job tables are made after the wait of retire and not before it,
+// 1,188 with new memory each time as well.
 int allocate(BatchPlan &bp, size_t bytes)
 {
     if (!serves(bp.mem_bytes, bytes)) {
@@ -501,7 +518,9 @@ int build(hmm_ctx *ctx, BatchPlan &bp, hipStream_t st)
         o_e[ci] = take(sizeof(long long) * KP * np);
         o_s[ci] = take(sizeof(long long) * np);
     }
-    int rc = allocate(bp, off);
+    // (the tables so far were made while the old plan may still be running)
+    int rc = retire(ctx, bp);
+    if (rc == HMM_OK) rc = allocate(bp, off);
     if (rc != HMM_OK) return rc;
     char *base = static_cast<char *>(bp.mem);
     bp.sets = reinterpret_cast<SetDesc *>(base + o_sets);
@@ -743,19 +762,8 @@ int get_plan(hmm_ctx *ctx, int n, const int32_t *K, const int64_t *T, const int6
         return capturing(st) ? HMM_E_DEVICE : set_pointers(*old, params, flag, xy, out, st);
     }
     if (capturing(st)) return HMM_E_DEVICE;
-    // launches, copies and graph replays of the old plan are over before
-    // anything it owns is given back or taken over
-    if (old && hipDeviceSynchronize() != hipSuccess) return HMM_E_DEVICE;
     BatchPlan *bp = new (std::nothrow) BatchPlan;
     if (!bp) return HMM_E_NOMEM;
-    if (old) {
-        std::swap(bp->mem, old->mem);
-        std::swap(bp->mem_bytes, old->mem_bytes);
-        std::swap(bp->host, old->host);
-        std::swap(bp->host_bytes, old->host_bytes);
-        batch_plan_free(old);
-        ctx->batch = nullptr;
-    }
     bp->n = n;
     bp->algo = algo;
     bp->K.assign(K, K + n);
