@@ -32,9 +32,9 @@
 // column of log2 Gamma stays in registers, the vector goes round through LDS,
 // the backpointers of a segment (bytes) stay in LDS.  What bounds it: VALU
 // issue (K = 25: 100 instructions a step, 160 with the backpointers, of which
-// 50 are the comparisons and selects of the argmax), and a step's chain of
-// LDS round trip, additions and row maxima, 0.37 us, where a SIMD holds only
-// one wavefront.  K = 25, T = 1e6: 1.55 -> 0.33 ms for the call (0.27 without
+// 50 are the comparisons and selects of the argmax; 68 % of the SIMDs' time at
+// T = 1e6), and a step's chain of LDS round trip, additions and row maxima, 0.37
+// us, where a SIMD holds only one wavefront (K = 64, T = 105,000: 47 %).  K = 25, T = 1e6: 1.55 -> 0.34 ms for the call (0.28 without
 // the score's flat vectors), K = 64, T = 105,000: 3.2 -> 0.23 ms.
 #pragma once
 
@@ -373,6 +373,7 @@ __global__ __launch_bounds__(64) void k_vit_chain(VitChain v, int mode)
             if constexpr (KIND == 2) {
                 vit_lds_sync();
                 if (l < n && rc + l < len) v.mx[t0 + rc + l] = reinterpret_cast<const float *>(obx)[6 * l];
+                vit_lds_sync();   // the next chunk's observations (another type) come after these reads
             }
         }
     };
