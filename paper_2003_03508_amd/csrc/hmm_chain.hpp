@@ -127,7 +127,8 @@ static_assert(sizeof(StateConst) == 64, "k_chain reads the constants as 8 double
 //    walker with two stagers (the latency of a step decides), longer ones two
 //    pairs.
 //  K > 32: two pairs, and for long sequences four (two wavefronts per SIMD:
-//    15 % more throughput at K = 80, where the walker is the longer one).
+//    15 % more throughput at K = 80, where the walker is the longer one; MFMA
+//    55 % and VALU issue 40 % of the SIMDs' time).
 struct ChainShape {
     int NP, NS;
     int64_t segs() const { return 16 * (int64_t)NP; }

@@ -473,10 +473,13 @@ __global__ __launch_bounds__(128) void k_post_scan_level(ScanLevel s)
 // Waves per workgroup of the local pass (its LDS grows with KB).
 template <int KB> constexpr int post_waves() { return 2; }
 // Segments per wavefront of the local passes, KB <= 32: lane group h (KB
-// lanes) holds one, its lanes the states.  What bounds these passes is LDS:
-// each step reads whole vectors of KB floats (the forward pass one, the
-// backward pass three), 8 cycles per 16-byte read of a wavefront whatever its
-// lanes share, so two (four) segments per read halve (quarter) the time.
+// lanes) holds one, its lanes the states.  With one segment a wavefront LDS
+// bounds these passes: each step reads whole vectors of KB floats (the forward
+// pass one, the backward pass three), 8 cycles per 16-byte read of a wavefront
+// whatever its lanes share, so two (four) segments per read halve (quarter) that.
+// Now VALU issue takes 47 % (forward) and 53 % (backward) of the SIMDs' time, LDS
+// 13 % and 39 %; a step's chain of LDS round trips and sums is what the two
+// wavefronts of a SIMD wait for otherwise.
 // The sums run over K rounded up to a multiple of four (KK).  Forward and
 // backward pass together, K = 25, T = 300,007: 224 -> 140 us; K = 20, T =
 // 500,000: 334 -> 173 us, the same bits.  The forward pass stages the emissions
