@@ -234,7 +234,6 @@ int loglik_impl(hmm_ctx *ctx, int kind, int32_t K, const double *delta, const do
     d.T = T;
     d.L = pl.L;
     d.K = K;
-    d.pad = 0;
     rc = run_single(ctx, ctx->ws, ks, d, pl, ly, cp, st);
     if (rc != HMM_OK) return rc;
     if (kind == kEmisPoisson && T > 0) {
@@ -453,7 +452,6 @@ int hmm_loglik_noalloc(int32_t K, const double *delta, const double *Gamma, cons
     d.T = T;
     d.L = pl.L;
     d.K = K;
-    d.pad = 0;
     rc = run_single(nullptr, ws, ks, d, pl, ly, cp, st);
     if (rc != HMM_OK) return rc;
     return launch_status();

@@ -551,6 +551,7 @@ int build(hmm_ctx *ctx, BatchPlan &bp, hipStream_t st)
         c.E = reinterpret_cast<long long *>(base + o_e[ci]);
         c.S = reinterpret_cast<long long *>(base + o_s[ci]);
     }
+    const int64_t total = std::accumulate(bp.T.begin(), bp.T.end(), int64_t(0));
     std::vector<SetDesc> hs(n);
     std::vector<PrepJob> hp(n);
     std::vector<int> hc(n);
@@ -570,7 +571,6 @@ int build(hmm_ctx *ctx, BatchPlan &bp, hipStream_t st)
         d.T = bp.T[s];
         d.L = c->serial ? 0 : c->L;
         d.K = bp.K[s];
-        d.pad = 0;
         PrepJob &pj = hp[s];
         pj.params = bp.params + bp.param_off[s];
         pj.sc = reinterpret_cast<StateConst *>(base + o_sc[s]);
@@ -583,7 +583,7 @@ int build(hmm_ctx *ctx, BatchPlan &bp, hipStream_t st)
             ly.vs = o_vs[s];
             ly.ve = o_ve[s];
             ly.part = o_part[s];
-            set_chain(&d, base, ly, cps[s]);
+            set_chain(&d, base, ly, cps[s], total);
             pj.chain = d.fail;
         }
         pj.max_stay = chain_max_stay(cps[s].q);

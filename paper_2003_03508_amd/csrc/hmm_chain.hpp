@@ -101,13 +101,11 @@ __device__ __forceinline__ bool chain_hopeless(float diff, int steps, int left, 
 // Reruns of a walker most of whose starts differ: the chain forgets slowly
 // everywhere, so the starts checked across walkers differ too and the second
 // launch walks everything again.  After the first pass n reruns cost
-// W + (2 n + 1) q steps, the segment products behind some 8 q (K = 20, T =
-// 20,000..200,000, q = 32..49: 8 to 10 q; K = 25, T = 10^6, q = 122: 10 q; K =
-// 40: 11 q; K = 80, q = 32: 7 q).
-__device__ __forceinline__ int chain_slow_repairs(int W, int q)
+// W + (2 n + 1) q steps; they are worth it while the segment products behind
+// would take longer.
+__device__ __forceinline__ int chain_slow_repairs(int W, int q, int product_steps)
 {
-    const int n = (7 * q - W) / (2 * q);
-    return n < 0 ? 0 : (n < kChainRepairs ? n : kChainRepairs);
+    return min(max(0, (product_steps - W - q) / (2 * q)), kChainRepairs);
 }
 
 // s parallel to e: |s - r e| <= tol s with r = ss / es (ss, es the sums of
@@ -803,10 +801,12 @@ __device__ __forceinline__ void chain_body(const SetDesc &d, int64_t wg, int mod
         mism = __any(inner && !ok) || !sound;
         int verdict = 0;   // bit 0: run again; bit 1: give the set back
         if (mism) {
-            const bool slow = last >= kChainCols / 2 && 2 * differ > last;
-            const int left = max(0, (slow ? chain_slow_repairs(W, (int)q) : kChainRepairs) - pass);
-            const bool end = !sound || (pass > 0 && sum > 0.5f * before) ||
-                             chain_hopeless(diff, W + pass * rel_end, left * rel_end, slow ? 1.f : 1.5f);
+            // most starts differ and the products cost little: strictly by the rate
+            const int most = chain_slow_repairs(W, (int)q, d.product_steps);
+            const bool strict = last >= kChainCols / 2 && 2 * differ > last && most < kChainRepairs;
+            const int left = max(0, (strict ? most : kChainRepairs) - pass);
+            const bool end = !sound || (strict && pass > 0 && sum > 0.5f * before) ||
+                             chain_hopeless(diff, W + pass * rel_end, left * rel_end, strict ? 1.f : 1.5f);
             verdict = end ? 3 : 1;
         } else if (!settled && sum > chain_budget((int64_t)(last + 1) * q, part)) {
             verdict = 1;

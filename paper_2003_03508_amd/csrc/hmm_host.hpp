@@ -487,9 +487,20 @@ inline hipError_t launch_fold(const void *fn, unsigned grid, int W2, size_t lds,
     return hipLaunchKernel(fn, dim3(grid), dim3(64 * W2), args, lds, st);
 }
 
-// Puts the chain state of a set (layout ly at ws) into its descriptor.
-inline void set_chain(SetDesc *d, void *ws, const Layout &ly, const ChainPlan &cp)
+// What the segment products of a launch with T observations in all take, in
+// steps of the chains of K states (measured: K = 20, T = 20,000 / 200,000 270 /
+// 340; K = 25, T = 105,000 / 10^6 420 / 1,290; K = 40, T = 105,000 440; K = 80,
+// T = 20,000 / 400,000 230 / 1,200).
+inline int chain_product_steps(int K, int64_t T)
 {
+    return (int)std::min(1.0e6, 200.0 + 3.5e-5 * (double)K * (double)T);
+}
+
+// Puts the chain state of a set (layout ly at ws) into its descriptor; T: the
+// observations of all sets of the launch.
+inline void set_chain(SetDesc *d, void *ws, const Layout &ly, const ChainPlan &cp, int64_t T)
+{
+    d->product_steps = chain_product_steps(d->K, T);
     d->fail = at<int>(ws, ly.chain);
     d->warm = at<int>(ws, ly.chain) + 1;
     d->vs = at<float>(ws, ly.vs);
@@ -545,7 +556,7 @@ inline int run_single(hmm_ctx *ctx, void *ws, const KernelSet &ks, SetDesc d, co
     const ChainShape shape = chain_shape(d.K, cp.big);
     if (chain) {
         if (allow_lds(chain, shape.lds(d.K)) != HMM_OK) return HMM_E_DEVICE;
-        set_chain(&d, ws, ly, cp);
+        set_chain(&d, ws, ly, cp, d.T);
     }
     if (ev0) (void)hipEventRecord(ev0, st);
     if (chain && launch_chain(chain, cp, shape, st, d) != hipSuccess) return HMM_E_DEVICE;

@@ -463,7 +463,8 @@ struct SetDesc {
     int *status;             // the set's status word
     double *out;             // the set's ln L
     int64_t T, L;            // observations, segment length
-    int K, pad;
+    int K;
+    int product_steps = 0;   // what the products cost in steps of the chains (chain_product_steps)
     // segment chains (k_chain); fail null: the set has none.  Where *fail is 0
     // after them, the segment and fold kernels of the product path return at
     // once and the final one adds up part.

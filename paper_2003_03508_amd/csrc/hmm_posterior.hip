@@ -1317,7 +1317,6 @@ int posterior_impl(hmm_ctx *ctx, int32_t K, const double *delta, const double *G
     sd.T = T;
     sd.L = L;
     sd.K = K;
-    sd.pad = 0;
     const size_t rb = (size_t)region_bytes(KP), rb_seg = post_seg_lds(ks);
     if (allow_lds(ks.seg1, rb_seg) != HMM_OK || allow_lds(ks.fold1, rb * G) != HMM_OK) return HMM_E_DEVICE;
     // segment products (one wavefront per workgroup), group levels, ln L
