@@ -630,7 +630,7 @@ __device__ __forceinline__ void chain_body(const SetDesc &d, int64_t wg, int mod
             chain_barrier();
             const int any = verdicts();
             chain_barrier();
-            if (any != 1 || pass == kChainRepairs) break;
+            if (any != 1) break;
         }
         if (__any(sg.bad) && lane == 0) atomicOr(d.status, kBadData);
         return;
@@ -799,13 +799,15 @@ __device__ __forceinline__ void chain_body(const SetDesc &d, int64_t wg, int mod
         part += kLn2 * (double)stot;
         const bool sound = fabs(part) < __builtin_inf();   // not L = 0, nothing overflowed
         mism = __any(inner && !ok) || !sound;
-        int verdict = 0;   // bit 0: run again; bit 1: give the set back
+        // bit 0: run again; bit 1: give the set back.  At most kChainRepairs runs
+        // for differences above the tolerance, and one of each walker for their sum
+        int verdict = 0;
         if (mism) {
             // most starts differ and the products cost little: strictly by the rate
             const int most = chain_slow_repairs(W, (int)q, d.product_steps);
             const bool strict = last >= kChainCols / 2 && 2 * differ > last && most < kChainRepairs;
             const int left = max(0, (strict ? most : kChainRepairs) - pass);
-            const bool end = !sound || (strict && pass > 0 && sum > 0.5f * before) ||
+            const bool end = !sound || pass >= kChainRepairs || (strict && pass > 0 && sum > 0.5f * before) ||
                              chain_hopeless(diff, W + pass * rel_end, left * rel_end, strict ? 1.f : 1.5f);
             verdict = end ? 3 : 1;
         } else if (!settled && sum > chain_budget((int64_t)(last + 1) * q, part)) {
@@ -817,7 +819,7 @@ __device__ __forceinline__ void chain_body(const SetDesc &d, int64_t wg, int mod
         chain_barrier();
         const int any = verdicts();
         chain_barrier();
-        if (any != 1 || pass == kChainRepairs) break;
+        if (any != 1) break;
         // again from the first observation, each segment from its neighbour's end
         const int sh = -fexp(pes);
 #pragma unroll

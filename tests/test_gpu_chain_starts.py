@@ -117,3 +117,19 @@ def test_one_slow_state_is_served(binding, ctx, product, K, T, slow):  # noqa: F
     prm.p[slow] = 0.001
     obs = synth.sample_path(np.random.default_rng(6), prm, T)
     assert_close(served(binding, ctx, product, prm, obs, quiet=True), ref(prm, obs), (K, T, slow))
+
+
+@pytest.mark.parametrize("K", [20, 26, 40])
+@pytest.mark.parametrize("there,back,p", [(0.004625, 0.087875, (0.15, 0.02)), (0.0035, 0.0665, (0.2, 0.1)),
+                                          (0.010125, 0.057375, (0.1, 0.02))])
+def test_flat_starts_after_the_last_rerun(binding, ctx, there, back, p, K):  # noqa: F811
+    """Groups that exchange so slowly that a segment's start meets the tolerance
+    only in the last rerun: 64-bit bias 1.8e-6..3.6e-6 of ln L.  In a batch with a
+    long record, whose products cost enough for three reruns."""
+    prm, obs = two_groups(K, 8192)
+    prm.Gamma = exchange(K, there, back)
+    prm.p = np.where(np.arange(K) < K // 2, *p)
+    sets = [(prm, obs), synth.make(K, 200_000, 3)]
+    out = ctx.loglik_batched(**binding.batch_to_device(synth.pack(sets))).cpu().numpy()
+    for i, s in enumerate(sets):
+        assert_close(float(out[i]), ref(*s), (K, i))
