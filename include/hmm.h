@@ -102,7 +102,7 @@ typedef enum {
      * more than the products alone.  Both give ln L within FP32 rounding:
      * about 1e-9 |ln L| in records with events; where the same observation
      * recurs (a record without events) its rounding recurs too, and either is
-     * off by up to 2e-7 nats per observation.  Used for K > 25 from T = 64,
+     * off by up to 5e-7 nats per observation.  Used for K > 25 from T = 64,
      * K > 16 from T = 1000, smaller K from T = 10^6 (K > 4) or 4 10^6, where it
      * is the faster one. */
     HMM_BLOCKED_F32 = 1,

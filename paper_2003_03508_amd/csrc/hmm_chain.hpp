@@ -72,7 +72,7 @@ __device__ __forceinline__ int64_t scalar(int64_t x)
 // What a walker's starts may differ by in sum without another run: obs
 // observations, ln: its part of ln L.  FP32 rounds every entry at every
 // observation, and where an observation recurs so does its rounding: ln L of a
-// record without events is off by 0.1..2e-7 per observation (segment products
+// record without events is off by 0.1..5e-7 per observation (segment products
 // and vectors alike, K = 20..80).
 __device__ __forceinline__ float chain_budget(int64_t obs, double ln)
 {
